@@ -280,6 +280,19 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
         d.hy_V = b.take<double>(E); d.hy_Sx = b.take<double>(E); d.hy_Sy = b.take<double>(E); d.hy_Sz = b.take<double>(E);
         d.hy_w = b.take<double>(E); d.hy_dl = b.take<double>(E); d.hy_g = b.take<double>(E); d.hy_phi = b.take<double>(E);
     }
+    {
+        const PartsHost &P = mesh_parts(m);
+        d.res_G = P.G; d.res_W = P.W; d.res_n = P.n_max; d.res_local = P.local_max;
+        if (P.G > 0) {
+            d.res_start = b.take<int32_t>(P.start.size()); d.res_hstart = b.take<int32_t>(P.hstart.size());
+            d.res_far = b.take<int32_t>(P.far.size()); d.res_shown = b.take<int32_t>(P.shown.size());
+            d.res_fin = b.take<int32_t>(P.G);
+            d.res_cell = b.take<int32_t>(N); d.res_fe = b.take<int32_t>(P.fe.size());
+            d.res_idx = b.take<uint16_t>(P.idx.size()); d.res_halo = b.take<int32_t>(P.halo.size());
+            d.res_slots = b.take<double>(kResSlotWords);
+            d.res_gen = b.take<int32_t>(1);
+        }
+    }
     d.red_stride = (int32_t)(((N + kBlock - 1) / kBlock + 7) / 8 * 8);
     d.red_stride2 = (d.red_stride + kGroup - 1) / kGroup;
     d.partials = b.take<double>((size_t)kMaxRed * d.red_stride);
@@ -419,6 +432,7 @@ struct Group {
     Poller *poll;
     hipStream_t s;
     std::shared_ptr<GraphCache> graphs = std::make_shared<GraphCache>();
+    std::shared_ptr<Group> rest;   // the cases whose pressure solve runs launched iterations, where others do not
     explicit Group(fvm_case *c, hipStream_t st) : poll(&c->poll), s(st)
     {
         cs.push_back(c);
@@ -555,6 +569,12 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     }
     UPCHK(up(d.sell_off, m->sell_off, s)); UPCHK(up(d.sell_mir, m->sell_mir, s));
     UPCHK(up(d.sell_fe, m->sell_fe, s)); UPCHK(up(d.sell_col, m->sell_col, s));
+    if (d.res_G > 0) {
+        const PartsHost &P = mesh_parts(*m);
+        UPCHK(up(d.res_start, P.start, s)); UPCHK(up(d.res_hstart, P.hstart, s)); UPCHK(up(d.res_cell, P.cell, s));
+        UPCHK(up(d.res_fe, P.fe, s)); UPCHK(up(d.res_idx, P.idx, s)); UPCHK(up(d.res_halo, P.halo, s));
+        UPCHK(up(d.res_far, P.far, s)); UPCHK(up(d.res_shown, P.shown, s));
+    }
     if (d.amg_nl > 0) {
         const AmgHost &A = mesh_amg(*m);
         if (d.amg_nc > kAmgDenseMax)
@@ -590,8 +610,10 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     UPCHK(hipMemsetAsync(d.ticket, 0, 64 * sizeof(unsigned int), s));
     UPCHK(hipMemsetAsync(d.gticket, 0, d.red_stride2 * sizeof(unsigned int), s));
     UPCHK(hipMemsetAsync(d.ks, 0, kNumKs * sizeof(KState), s));
+    if (d.res_G > 0) UPCHK(hipMemsetAsync(d.res_fin, 0, sizeof(int32_t) * d.res_G, s));
     const Group g(c, s);
     launch_init_partials(g.bs, s);
+    launch_res_reset(g.bs, 0, s);
     launch_geometry(g.bs, s);
     if (d.hy_K > 0) launch_hybrid_geometry(g.bs, s);
     UPCHK(hipMemsetAsync(d.U, 0, 3 * (size_t)m->N * sizeof(double), s));
@@ -812,11 +834,179 @@ void record_iters(Group &g, const std::vector<KState> &res, int first, int count
     }
 }
 
+// ---- resident pressure CG (resident_cg.h) ----
+// The workgroups of such a launch wait for each other, so all of them must
+// be on the device at once: a launch takes at most one per CU, and a launch
+// waits (on the device) for the one before it on the same device, on
+// whichever stream and from whichever thread that was enqueued.
+struct ResidentDevice {
+    int usable = -1;           // -1: not looked at yet
+    hipEvent_t last = nullptr; // recorded after the latest launch
+    bool any = false;
+};
+std::mutex g_res_mu;
+ResidentDevice g_res_dev[64];
+// limit of one wait between workgroups, in 10 ns: far above any wait behind
+// other kernels of this library
+constexpr long kResWaitTicks = 1000000000L;
+thread_local long t_res_ticks = kResWaitTicks;
+thread_local bool t_res_leave_out = false;
+
+// state of the current device (g_res_mu held); nullptr when not usable
+ResidentDevice *resident_device()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    ResidentDevice &R = g_res_dev[dev];
+    if (R.usable < 0) {
+        int cus = 0;
+        R.usable = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= kResParts &&
+                   res_prepare() == 0 && hipEventCreateWithFlags(&R.last, hipEventDisableTiming) == hipSuccess;
+        (void)hipGetLastError();
+    }
+    return R.usable ? &R : nullptr;
+}
+
+// a name for the next solve, > 0 (finished parts record it)
+int resident_serial()
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    static int serial = 0;
+    serial = serial == INT32_MAX ? 1 : serial + 1;
+    return serial;
+}
+
+bool resident_usable()
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    return resident_device() != nullptr;
+}
+
+// cases that share a launch, and which part each workgroup holds: workgroup
+// 8 k + x runs on XCD x, so a group of parts takes workgroups of one x
+struct ResidentBatch {
+    BatchSet bs;
+    int fill[kResGroups] = {};
+    uint8_t cs[kResParts], pt[kResParts];
+    ResidentBatch()
+    {
+        bs.n = 0;
+        std::memset(cs, 255, sizeof(cs));
+        std::memset(pt, 0, sizeof(pt));
+    }
+    // false when the case's groups do not fit beside what is there
+    bool add(const DevCase *self, const DevCase &d)
+    {
+        const int G = d.res_G, ng = res_groups(G);
+        if (bs.n > 0 && bs.host[0]->res_W != d.res_W) return false;
+        int at[kResGroups], sum[kResGroups];
+        std::copy(fill, fill + kResGroups, sum);
+        for (int g = 0; g < ng; ++g) {
+            const int size = res_group_first(g + 1, G) - res_group_first(g, G);
+            at[g] = -1;
+            // the fullest XCD that still has room
+            for (int x = 0; x < kResGroups; ++x)
+                if (sum[x] + size <= kResGroup && (at[g] < 0 || sum[x] > sum[at[g]])) at[g] = x;
+            if (at[g] < 0) return false;
+            sum[at[g]] += size;
+        }
+        for (int part = 0; part < G; ++part) {
+            const int x = at[res_group_of(part, G)], b = kResGroups * fill[x]++ + x;
+            cs[b] = (uint8_t)bs.n;
+            pt[b] = (uint8_t)part;
+        }
+        batch_add(bs, self, &d);
+        return true;
+    }
+};
+
+fvm_status resident_launch(ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    ResidentDevice *R = resident_device();
+    if (!R) return fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
+    if (R->any) HIPCHK(hipStreamWaitEvent(s, R->last, 0));
+    if (t_res_leave_out)
+        for (int b = kResParts - 1; b >= 0; --b)
+            if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
+    launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipEventRecord(R->last, s));
+    R->any = true;
+    return FVM_OK;
+}
+
+fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res);
+
+// the cases `idx` of the group (all resident), packed into launches: largest
+// first, each into the first launch with room
+fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solver_ctl *ctl, int serial)
+{
+    std::vector<std::unique_ptr<ResidentBatch>> batches;
+    std::vector<int> order(idx);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return g.cs[a]->d.res_G > g.cs[b]->d.res_G; });
+    for (int i : order) {
+        const DevCase &d = g.cs[i]->d;
+        bool placed = false;
+        for (auto &b : batches) placed = placed || b->add(d.self, d);
+        if (!placed) {
+            batches.emplace_back(new ResidentBatch());
+            batches.back()->add(d.self, d);
+        }
+    }
+    for (auto &b : batches) {
+        fvm_status st = resident_launch(*b, ctl, serial, g.s);
+        if (st != FVM_OK) return st;
+    }
+    return FVM_OK;
+}
+
 // One solve for every case of the group.  kind 0: momentum BiCG (systems
 // 0..2), kind 1: pressure CG (system 3).  ctl_src selects the controls:
 // 0/1 = the cases' own momentum / pressure controls, 2 = *ctl.
-// FVM_MIXED cases run the mixed-precision variants.
+// FVM_MIXED cases run the mixed-precision variants.  Jacobi pressure solves
+// run resident where the case has parts for it; a case's choice does not
+// depend on the others of the group.
 fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res)
+{
+    const int precond = ctl_src == 2 ? ctl->precond : g.cs[0]->o.p_ctl.precond;
+    std::vector<int> on;
+    if (kind == 1 && precond == FVM_PC_JACOBI && g.cs[0]->o.precision == FVM_FP64 && resident_usable())
+        for (int i = 0; i < g.n(); ++i)
+            if (g.cs[i]->d.res_G > 0) on.push_back(i);
+    if (on.empty()) return run_launched(g, kind, ctl_src, ctl, res);
+    const int serial = resident_serial();
+    fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial);
+    if (st != FVM_OK) return st;
+    if ((int)on.size() < g.n()) {
+        if (!g.rest) {
+            std::vector<fvm_case *> off;
+            for (auto *c : g.cs)
+                if (c->d.res_G == 0) off.push_back(c);
+            g.rest = std::make_shared<Group>(off.data(), (int)off.size(), g.poll, g.s);
+        }
+        st = run_launched(*g.rest, kind, ctl_src, ctl, res);
+        if (st != FVM_OK) return st;
+    }
+    st = snapshot(g, res);
+    if (st != FVM_OK) return st;
+    std::vector<fvm_case *> late;
+    for (int i : on)
+        if (res[(size_t)i * kNumKs + kNumKs - 1].pad[0]) late.push_back(g.cs[i]);
+    if (!late.empty()) {
+        // a wait ran out: these solves begin again as launched iterations
+        Group again(late.data(), (int)late.size(), g.poll, g.s);
+        launch_res_reset(again.bs, serial, g.s);
+        st = run_launched(again, kind, ctl_src, ctl, res);
+        if (st == FVM_OK) st = snapshot(g, res);
+        if (st != FVM_OK) return st;
+    }
+    record_iters(g, res, 3, 1, kind);
+    return FVM_OK;
+}
+
+// the same as launches per iteration
+fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res)
 {
     const BatchSet &bs = g.bs;
     hipStream_t s = g.s;
@@ -1027,6 +1217,15 @@ fvm_status rollback_failed(Group &g, const std::vector<fvm_step_info> &info)
 
 }  // namespace
 
+// for tests of the path that begins a solve again: the calling thread's wait
+// limit (ticks <= 0: the usual one), and whether its resident launches leave
+// out the last workgroup, so that every other one waits until the limit
+extern "C" void fvm_resident_test_hook(long ticks, int leave_out)
+{
+    t_res_ticks = ticks > 0 ? ticks : kResWaitTicks;
+    t_res_leave_out = ticks > 0 && leave_out;
+}
+
 // ---------------------------------------------------------------------------
 // public: PISO, SIMPLE, stand-alone pressure solve, batch
 // ---------------------------------------------------------------------------
@@ -1165,7 +1364,11 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
     unsigned char *gt = take(sizeof(unsigned int) * (size_t)d.red_stride2);
     unsigned char *tk = take(sizeof(unsigned int) * 64);
     unsigned char *ks = take(sizeof(KState) * kNumKs);
+    unsigned char *rs = d.res_G > 0 ? take(sizeof(double) * kResSlotWords) : nullptr;
+    unsigned char *rg = d.res_G > 0 ? take(sizeof(int32_t)) : nullptr;
     if (h) {
+        h->res_slots = reinterpret_cast<double *>(rs);
+        h->res_gen = reinterpret_cast<int32_t *>(rg);
         h->self = reinterpret_cast<DevCase *>(self);
         h->partials = reinterpret_cast<double *>(p1);
         h->partials2 = reinterpret_cast<double *>(p2);
@@ -1217,13 +1420,30 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     launch_gather_faces(bs, gamma, d.phiH, s);
     launch_p_system_from_gamma(bs, d.phiH, rhs, s);
     HIPCHK(hipMemcpyAsync(d.p, p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
-    launch_set_ctl(bs, 3, 1, 2, ctl->tol, ctl->rel_tol, ctl->max_iter, s);
-    launch_pcg_init(bs, 0, s);
+    KState ks{};
+    bool launched = true;
+    if (d.res_G > 0 && resident_usable()) {
+        ResidentBatch rb;
+        rb.add(h.self, h);
+        launch_res_reset(bs, 0, s);
+        const int serial = resident_serial();
+        fvm_status st = resident_launch(rb, ctl, serial, s);
+        if (st != FVM_OK) return st;
+        KState all[kNumKs];
+        HIPCHK(hipMemcpyAsync(all, h.ks, sizeof(all), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        launched = all[kNumKs - 1].pad[0] != 0;   // a wait ran out: begin again
+        if (launched) launch_res_reset(bs, serial, s);
+        else ks = all[3];
+    }
+    if (launched) {
+        launch_set_ctl(bs, 3, 1, 2, ctl->tol, ctl->rel_tol, ctl->max_iter, s);
+        launch_pcg_init(bs, 0, s);
+    }
     // direct launches in chunks, the stop flag read back after each chunk
     // (iterations past it return at once); no graph, no pinned buffer
-    KState ks{};
     const long limit = (long)ctl->max_iter + 1;
-    for (long issued = 0;;) {
+    for (long issued = 0; launched;) {
         const long n = std::min<long>(8, limit - issued);
         for (long k = 0; k < n; ++k) launch_pcg_iter(bs, 0, (int)(k & 1), s);
         issued += n;

@@ -20,6 +20,35 @@ constexpr int kAmgCoarseMax = 128;    // coarsen while a level has more cells
 constexpr int kAmgDenseMax = 512;     // largest coarsest level (dense inverse)
 constexpr int kAmgTailLds = 64 * 1024;   // LDS bytes of the fused smallest-levels launch
 
+// Parts of the mesh for the resident pressure CG (resident_cg.h), built once
+// and cached; G == 0 where the mesh has no such form (too many cells, more
+// than 6 neighbours per cell, halos larger than the LDS)
+struct PartsHost;
+const PartsHost &mesh_parts(const fvm_mesh &m);
+constexpr int kResCells = 4096;       // largest part (512 threads of 8 cells)
+constexpr int kResParts = 256;        // most parts of a case: one workgroup per CU
+constexpr int kResGroup = 32;         // parts of a group: the CUs of an XCD
+constexpr int kResGroups = kResParts / kResGroup;
+constexpr int kResLocal = 7680;       // own cells and halo of a part: 12 bytes of LDS for each, 16 per own cell
+constexpr int kResGens = 4;           // generations of reduction slots
+constexpr int kResMaxSum = 4;         // sums per reduction (slots laid out)
+constexpr size_t kResSlotWords = (size_t)kResGens * kResMaxSum * kResGroups * (kResGroup + kResGroups);
+#ifdef __HIPCC__
+#define RES_HD __host__ __device__
+#else
+#define RES_HD
+#endif
+// the G parts of a case in groups of nearly equal size: their number, the
+// group of a part, and a group's first part
+RES_HD inline int res_groups(int G) { return (G + kResGroup - 1) / kResGroup; }
+RES_HD inline int res_group_first(int g, int G) { return (int)((long)g * G / res_groups(G)); }
+RES_HD inline int res_group_of(int part, int G)
+{
+    int g = (int)((long)part * res_groups(G) / G);
+    while (res_group_first(g + 1, G) <= part) ++g;
+    return g;
+}
+
 struct ihipStream_t;
 typedef struct ihipStream_t *hipStream_t;
 
@@ -59,6 +88,21 @@ struct AmgLevelHost {
 };
 struct AmgHost {
     std::vector<AmgLevelHost> L;
+};
+
+// Cells grouped into G compact parts (recursive bisection of the cell
+// centres): part p holds the positions start[p] .. start[p+1], cell[pos] is
+// the cell there.  A part's first far[p] cells lie in the halo of a part of
+// another group, its first shown[p] in the halo of any other part; ascending
+// within each of the three ranges.  A part's entries are slot-major
+// (W slots, its n cells consecutive, at W * start[p] + k * n + l for its cell
+// l), a cell's in ascending column: fe as sell_fe, idx the neighbour's place
+// in the part's local vector (own cells, then the halo).  halo[hstart[p] ..]
+// lists the positions of the part's neighbours in other parts, ascending.
+struct PartsHost {
+    int32_t G = 0, W = 0, n_max = 0, local_max = 0;
+    std::vector<int32_t> start, hstart, far, shown, cell, fe, halo;
+    std::vector<uint16_t> idx;
 };
 
 struct fvm_mesh {
@@ -114,6 +158,7 @@ struct fvm_mesh {
     // slots mirrored from the upper ones, every neighbour inside the mesh
     int32_t sell_n7 = 0;
     mutable std::shared_ptr<AmgHost> amg;   // AMG hierarchy, built on first use
+    mutable std::shared_ptr<PartsHost> parts;   // parts of the resident CG, built on first use
 };
 
 // ---------------------------------------------------------------------------
@@ -234,6 +279,15 @@ struct DevCase {
     double *amg_cinv;
     double *amg_img;                             // [kAmgTailLds / 8] LDS image of the smallest levels
     double *amg_b[20], *amg_out[20];             // each level's right-hand side and result (host copies)
+    // resident pressure CG (PartsHost; res_G == 0: the case has none):
+    // reduction slots (kResSlotWords) and the generation the next solve
+    // starts with, the last solve each part finished; a solve whose waits ran out sets
+    // ks[kNumKs - 1].pad[0]
+    int32_t res_G, res_W, res_n, res_local;
+    int32_t *res_start, *res_hstart, *res_far, *res_shown, *res_fin, *res_cell, *res_fe, *res_halo;
+    uint16_t *res_idx;
+    double *res_slots;
+    int32_t *res_gen;
     // reductions
     double *partials;                            // [kMaxRed][red_stride]   level-1 slots
     double *partials2;                           // [kMaxRed][red_stride2]  level-2 slots
@@ -342,6 +396,18 @@ void launch_operator(const BatchSet &bs, int op, const double *in, double *out, 
 // r.z -> rho, beta
 void launch_amg_precond(const BatchSet &bs, int with_setup, hipStream_t s);
 void launch_hybrid_geometry(const BatchSet &bs, hipStream_t s);
+// resident pressure CG of the cases of bs (FP64, all with res_G > 0 and the
+// same res_W), workgroup b holding part pt[b] of case cs[b] (255: none): one
+// launch, ended by the stop tests.  ctl null: the cases' own pressure
+// controls; ticks: limit of a wait between workgroups in 10 ns; serial: a
+// name of the solve.  launch_res_reset: slots and state as at creation; with
+// a serial the parts that finished that solve get their start values back.
+// res_prepare: sets the kernels' LDS limit on the current device and checks
+// that a workgroup fits on a CU; 0 when usable.
+void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,
+                   int serial, hipStream_t s);
+void launch_res_reset(const BatchSet &bs, int serial, hipStream_t s);
+int res_prepare();
 // whole PISO steps, one workgroup per case (small orthogonal Jacobi/BiCG
 // cases, n_corr <= kSoloMaxCorr): grid = the batch's cases; the last
 // step's record is left in each case's Krylov state slots (see

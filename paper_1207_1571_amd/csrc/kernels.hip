@@ -2362,6 +2362,8 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
     }
 }
 
+#include "resident_cg.h"
+
 // ---------------------------------------------------------------------------
 // Whole PISO steps of small cases, one workgroup per case
 //
@@ -4020,6 +4022,59 @@ void launch_pcg_iter(const BatchSet &bs, int pc, int parity, hipStream_t s)
     if (pc == 1) launch_dic_precond(bs, 0, s);
     else if (pc == 2) launch_amg_precond(bs, 0, s);
 }
+
+namespace {
+// LDS of a part with `local` own and halo cells
+size_t res_lds_bytes(int local) { return (sizeof(double) + sizeof(int32_t)) * (size_t)local + 2 * sizeof(double) * kResCells; }
+
+typedef void (*ResKernel)(Batch, ResMap, ResCtl, long);
+// fewer cells per thread where every part is small: less code to walk
+template <int W>
+ResKernel res_kernel_u(int cells)
+{
+    return cells <= 2 * kResThreads ? k_res_cg<W, 2> : cells <= 4 * kResThreads ? k_res_cg<W, 4> : k_res_cg<W, 8>;
+}
+ResKernel res_kernel(int W, int cells) { return W == 4 ? res_kernel_u<4>(cells) : res_kernel_u<6>(cells); }
+}  // namespace
+
+int res_prepare()
+{
+    // every kernel may use the LDS of the largest part, and one workgroup of
+    // it fits on a CU
+    for (int W = 4; W <= 6; W += 2)
+        for (int U = 2; U <= 8; U *= 2) {
+            const void *k = (const void *)res_kernel(W, U * kResThreads);
+            const size_t lds = res_lds_bytes(kResLocal);
+            int blocks = 0;
+            if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+                hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, kResThreads, lds) != hipSuccess || blocks < 1) {
+                (void)hipGetLastError();
+                return 1;
+            }
+        }
+    return 0;
+}
+
+void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,
+                   int serial, hipStream_t s)
+{
+    Prof p("pcg_resident", s);
+    ResMap map;
+    int grid = 0, cells = 0, local = 0;
+    for (int b = 0; b < kResParts; ++b) {
+        map.cs[b] = cs[b];
+        map.pt[b] = pt[b];
+        if (cs[b] != 255) grid = b + 1;
+    }
+    for (int c = 0; c < bs.n; ++c) {
+        cells = std::max(cells, bs.host[c]->res_n);
+        local = std::max(local, bs.host[c]->res_local);
+    }
+    const ResCtl rc{ctl ? ctl->tol : 0.0, ctl ? ctl->rel_tol : 0.0, ctl ? ctl->max_iter : 0, ctl ? 1 : 0, serial};
+    hipLaunchKernelGGL(res_kernel(bs.host[0]->res_W, cells), dim3((unsigned)grid), dim3(kResThreads), res_lds_bytes(local), s,
+                       bs.b[SZ_CELL], map, rc, ticks);
+}
+void launch_res_reset(const BatchSet &bs, int serial, hipStream_t s) { run(k_res_reset, bs, SZ_CELL, s, serial); }
 
 void launch_mx_cvt(const BatchSet &bs, int kind, hipStream_t s) { run(k_mx_cvt, bs, SZ_MAXNF, s, kind); }
 

@@ -515,6 +515,144 @@ fvm_status build(const fvm_mesh_desc *d, fvm_mesh *m)
 
 }  // namespace
 
+namespace {
+
+struct PartCell {
+    double c[3];
+    int32_t i;
+};
+
+// the cells [a, a + n) into g parts of nearly equal size: split across the
+// longest extent of their centres, in proportion, until g == 1
+void bisect(PartCell *a, int32_t n, int32_t g, std::vector<int32_t> &size)
+{
+    if (g == 1) {
+        size.push_back(n);
+        return;
+    }
+    double lo[3], hi[3];
+    for (int k = 0; k < 3; ++k) lo[k] = hi[k] = a[0].c[k];
+    for (int32_t j = 1; j < n; ++j)
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = std::min(lo[k], a[j].c[k]);
+            hi[k] = std::max(hi[k], a[j].c[k]);
+        }
+    int ax = 0;
+    for (int k = 1; k < 3; ++k)
+        if (hi[k] - lo[k] > hi[ax] - lo[ax]) ax = k;
+    const int32_t gl = g / 2, nl = (int32_t)((int64_t)n * gl / g);
+    std::nth_element(a, a + nl, a + n, [ax](const PartCell &x, const PartCell &y) {
+        return x.c[ax] != y.c[ax] ? x.c[ax] < y.c[ax] : x.i < y.i;
+    });
+    bisect(a, nl, gl, size);
+    bisect(a + nl, n - nl, g - gl, size);
+}
+
+}  // namespace
+
+const PartsHost &mesh_parts(const fvm_mesh &m)
+{
+    if (m.parts) return *m.parts;
+    auto h = std::make_shared<PartsHost>();
+    const int32_t N = m.N;
+    const int32_t G = (N + kResCells - 1) / kResCells;
+    if (G > kResParts || m.sell_W > 6) {
+        m.parts = h;
+        return *h;
+    }
+    const int32_t W = m.sell_W <= 4 ? 4 : 6;
+    std::vector<PartCell> a(N);
+    for (int32_t i = 0; i < N; ++i) a[i] = PartCell{{m.C[i], m.C[(size_t)N + i], m.C[2 * (size_t)N + i]}, i};
+    std::vector<int32_t> size;
+    bisect(a.data(), N, G, size);
+    std::vector<int32_t> pos(N), part(N), mark(N, -1), where(N), found;
+    h->start.assign(1, 0);
+    h->hstart.assign(1, 0);
+    h->cell.resize(N);
+    for (int32_t p = 0, at = 0; p < G; ++p) {
+        for (int32_t j = at; j < at + size[p]; ++j) part[a[j].i] = p;
+        at += size[p];
+        h->start.push_back(at);
+        h->n_max = std::max(h->n_max, size[p]);
+    }
+    // order inside a part: cells read from other groups, from other parts of
+    // the group, the rest
+    std::vector<int32_t> group(G), keyed;
+    for (int32_t p = 0; p < G; ++p) group[p] = res_group_of(p, G);
+    for (int32_t p = 0; p < G; ++p) {
+        const int32_t p0 = h->start[p], n = size[p];
+        int32_t count[3] = {0, 0, 0};
+        keyed.resize(n);
+        for (int32_t l = 0; l < n; ++l) keyed[l] = a[p0 + l].i;
+        std::sort(keyed.begin(), keyed.end());
+        std::vector<uint8_t> cls(n, 2);
+        for (int32_t l = 0; l < n; ++l) {
+            const int32_t i = keyed[l];
+            auto read_by = [&](int32_t j) {
+                if (group[part[j]] != group[p]) cls[l] = 0;
+                else if (part[j] != p && cls[l] == 2) cls[l] = 1;
+            };
+            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k) read_by(m.own[m.losort[k]]);
+            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f) read_by(m.nei[f]);
+            count[cls[l]]++;
+        }
+        h->far.push_back(count[0]);
+        h->shown.push_back(count[0] + count[1]);
+        int32_t next[3] = {p0, p0 + count[0], p0 + count[0] + count[1]};
+        for (int32_t l = 0; l < n; ++l) {
+            pos[keyed[l]] = next[cls[l]];
+            h->cell[next[cls[l]]++] = keyed[l];
+        }
+    }
+    a = std::vector<PartCell>();
+    h->fe.assign((size_t)W * N, -1);
+    h->idx.assign((size_t)W * N, 0);
+    for (int32_t p = 0; p < G; ++p) {
+        const int32_t p0 = h->start[p], n = size[p];
+        found.clear();
+        auto others = [&](int32_t j) {
+            if (part[j] != p && mark[j] != p) {
+                mark[j] = p;
+                found.push_back(pos[j]);
+            }
+        };
+        for (int32_t l = 0; l < h->shown[p]; ++l) {
+            const int32_t i = h->cell[p0 + l];
+            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k) others(m.own[m.losort[k]]);
+            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f) others(m.nei[f]);
+        }
+        std::sort(found.begin(), found.end());
+        const int32_t H = (int32_t)found.size();
+        if (n + H > kResLocal) {
+            *h = PartsHost();
+            m.parts = h;
+            return *h;
+        }
+        for (int32_t k = 0; k < H; ++k) where[found[k]] = n + k;
+        auto local = [&](int32_t j) { return part[j] == p ? pos[j] - p0 : where[pos[j]]; };
+        for (int32_t l = 0; l < n; ++l) {
+            const int32_t i = h->cell[p0 + l];
+            size_t e = (size_t)W * p0 + l;
+            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k, e += n) {
+                const int32_t f = m.losort[k];
+                h->fe[e] = 2 * f + 1;
+                h->idx[e] = (uint16_t)local(m.own[f]);
+            }
+            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f, e += n) {
+                h->fe[e] = 2 * f;
+                h->idx[e] = (uint16_t)local(m.nei[f]);
+            }
+        }
+        h->halo.insert(h->halo.end(), found.begin(), found.end());
+        h->hstart.push_back((int32_t)h->halo.size());
+        h->local_max = std::max(h->local_max, n + H);
+    }
+    h->G = G;
+    h->W = W;
+    m.parts = h;
+    return *h;
+}
+
 extern "C" fvm_status fvm_mesh_create(const fvm_mesh_desc *desc, fvm_mesh **out)
 {
     if (!out) return fvm_fail(FVM_EINVAL, "mesh: null output");
