@@ -133,15 +133,16 @@ typedef struct {
 } fvm_case_opts;
 
 /* How piso_step and piso_step_batch run a case.  FVM_STEP_AUTO: a small
- * case (at most 32 768 cells, orthogonal mesh, Jacobi pressure CG, BiCG
- * momentum, at most 4 correctors, no non-orthogonal correctors) runs its
- * whole PISO steps, Krylov loops included, in one workgroup of one kernel
- * launch (many such cases side by side, one per compute unit), since at that
- * size launches and host round trips per Krylov iteration would cost more
- * than the arithmetic; any other case, and every case under
- * FVM_STEP_LAUNCHED, runs each phase of each iteration as a grid-wide launch.
- * Both give the method's result (they differ only in the order of the
- * floating-point sums). */
+ * mixed-precision case (at most 32 768 cells, at most 6 neighbours per cell,
+ * orthogonal mesh, Jacobi pressure CG, BiCG momentum, at most 4 correctors,
+ * no non-orthogonal correctors) runs its whole PISO steps, Krylov loops
+ * included, in one workgroup of one kernel launch (many such cases side by
+ * side, one per compute unit), since at that size launches and host round
+ * trips per Krylov iteration would cost more than the arithmetic; any other
+ * case, and every case under FVM_STEP_LAUNCHED, runs each phase as a
+ * grid-wide launch (the FP64 Jacobi pressure CG of up to 1M cells as one
+ * launch per solve).  Both give the method's result (they differ only in the
+ * order of the floating-point sums). */
 enum { FVM_STEP_AUTO = 0, FVM_STEP_LAUNCHED = 1 };
 
 typedef struct {

@@ -383,10 +383,13 @@ struct fvm_case {
     std::vector<fvm_patch> patches;
     Poller poll;
     int last_iters[4] = {0, 0, 0, 0};   // momentum, pressure, momentum inner; chunk sizing
-    // whole PISO steps in one workgroup (see FVM_STEP_AUTO)
+    // whole PISO steps in one workgroup (see FVM_STEP_AUTO).  FP64 cases of
+    // these sizes run launched phases around the resident pressure CG, which
+    // spreads a case over several CUs: a step of 15 500 cells takes 1.2 ms
+    // against 10.8 in one workgroup, one of 1 024 cells 1.2 against 2.4
     bool solo() const
     {
-        return o.step_kernel == FVM_STEP_AUTO && N <= kSoloMaxCells && !nonorth && o.n_non_orth_corr == 0 &&
+        return o.step_kernel == FVM_STEP_AUTO && o.precision == FVM_MIXED && N <= kSoloMaxCells && d.sell_W <= 6 && !nonorth && o.n_non_orth_corr == 0 &&
                o.n_corr <= kSoloMaxCorr && o.p_ctl.precond == FVM_PC_JACOBI && o.u_solver == FVM_SOLVER_BICG;
     }
 };

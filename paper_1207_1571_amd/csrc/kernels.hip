@@ -271,6 +271,83 @@ __device__ __forceinline__ T row_apply(const DevCase &d, int i, const T *__restr
     return (T)acc;
 }
 
+// row_apply for three components x, x + N, x + 2 N at once (those with
+// act[c]; the others' results are not set): faces, neighbours and
+// coefficients are read once instead of once per component, which is what
+// bounds a row (the index chain face -> neighbour -> value; a momentum solve
+// of 30^3 cells in one workgroup: 8.0 -> 5.1 ms).  Each component's sum is formed as row_apply forms it.
+template <class T>
+__device__ __forceinline__ void row_apply3(const DevCase &d, int i, const T *__restrict__ diag, const T *__restrict__ up,
+                                           const T *__restrict__ lo, const T *__restrict__ x, const int (&act)[3],
+                                           T (&y)[3])
+{
+    const long N = d.N;
+    const double dg = (double)diag[i];
+    double acc[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (act[c]) acc[c] = dg * (double)x[c * N + i];
+    const int f0 = d.own_start[i], f1 = d.own_start[i + 1];
+    for (int f = f0; f < f1; ++f) {
+        const double a = (double)up[f];
+        const int j = d.nei[f];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (act[c]) acc[c] += a * (double)x[c * N + j];
+    }
+    const int k0 = d.nbr_start[i], k1 = d.nbr_start[i + 1];
+    for (int k = k0; k < k1; ++k) {
+        const int f = d.losort[k];
+        const double a = (double)lo[f];
+        const int j = d.own[f];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (act[c]) acc[c] += a * (double)x[c * N + j];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (act[c]) y[c] = (T)acc[c];
+}
+
+// the rows of A x and A^T xt together (BiCG)
+template <class T>
+__device__ __forceinline__ void row_apply3_both(const DevCase &d, int i, const T *__restrict__ diag,
+                                                const T *__restrict__ up, const T *__restrict__ lo,
+                                                const T *__restrict__ x, const T *__restrict__ xt, const int (&act)[3],
+                                                T (&y)[3], T (&yt)[3])
+{
+    const long N = d.N;
+    const double dg = (double)diag[i];
+    double acc[3], acct[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (act[c]) {
+            acc[c] = dg * (double)x[c * N + i];
+            acct[c] = dg * (double)xt[c * N + i];
+        }
+    auto face = [&](double a, double at, int j) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (act[c]) {
+                acc[c] += a * (double)x[c * N + j];
+                acct[c] += at * (double)xt[c * N + j];
+            }
+    };
+    const int f0 = d.own_start[i], f1 = d.own_start[i + 1];
+    for (int f = f0; f < f1; ++f) face((double)up[f], (double)lo[f], d.nei[f]);
+    const int k0 = d.nbr_start[i], k1 = d.nbr_start[i + 1];
+    for (int k = k0; k < k1; ++k) {
+        const int f = d.losort[k];
+        face((double)lo[f], (double)up[f], d.own[f]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (act[c]) {
+            y[c] = (T)acc[c];
+            yt[c] = (T)acct[c];
+        }
+}
+
 // row sum of the off-diagonal coefficients plus the diagonal (A 1)_i
 __device__ __forceinline__ double row_sum(const DevCase &d, int i, const double *__restrict__ diag,
                                           const double *__restrict__ up, const double *__restrict__ lo)
@@ -939,14 +1016,13 @@ __global__ void __launch_bounds__(kBlock) k_bicg_spmv(Batch bt)
     const long N = d.N;
     double acc[3] = {0.0, 0.0, 0.0};
     for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock) {
+        T q[3], qt[3];
+        row_apply3_both<T>(d, i, v.diag, v.up, v.lo, v.p, v.pt, act, q, qt);
         for (int c = 0; c < 3; ++c) {
             if (!act[c]) continue;
-            const T *p = v.p + c * N, *pt = v.pt + c * N;
-            const T q = row_apply<T>(d, i, v.diag, v.up, v.lo, p);
-            const T qt = row_apply<T>(d, i, v.diag, v.lo, v.up, pt);
-            v.q[c * N + i] = q;
-            v.qt[c * N + i] = qt;
-            acc[c] += (double)pt[i] * (double)q;
+            acc[c] += (double)v.pt[c * N + i] * (double)q[c];
+            v.q[c * N + i] = q[c];
+            v.qt[c * N + i] = qt[c];
         }
     }
     __shared__ double tot[3];
@@ -1035,9 +1111,11 @@ __global__ void __launch_bounds__(kBlock) k_bicg_init(Batch bt, int stab)
     for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock) {
         const double a1 = row_sum(d, i, d.mdiag, d.upper, d.lower);
         const double dg = d.mdiag[i];
+        const int every[3] = {1, 1, 1};
+        double ax3[3];
+        row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.U, every, ax3);
         for (int c = 0; c < 3; ++c) {
-            const double *x = d.U + c * N;
-            const double ax = row_apply<double>(d, i, d.mdiag, d.upper, d.lower, x);
+            const double ax = ax3[c];
             const double b = d.rhs[c * N + i];
             const double r = b - ax;
             d.r[c * N + i] = r;
@@ -1101,13 +1179,15 @@ __global__ void __launch_bounds__(kBlock) k_bs_spmv_v(Batch bt)
     const Range rg = block_range(d.N, K);
     const long N = d.N;
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock)
+    for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock) {
+        double v[3];
+        row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.ph, act, v);
         for (int c = 0; c < 3; ++c) {
             if (!act[c]) continue;
-            const double v = row_apply<double>(d, i, d.mdiag, d.upper, d.lower, d.ph + c * N);
-            d.q[c * N + i] = v;
-            acc[c] += d.rt[c * N + i] * v;
+            acc[c] += d.rt[c * N + i] * v[c];
+            d.q[c * N + i] = v[c];
         }
+    }
     __shared__ double tot[3];
     if (reduce_last<3>(acc, d, K, tot) && threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) {
@@ -1162,14 +1242,16 @@ __global__ void __launch_bounds__(kBlock) k_bs_spmv_t(Batch bt)
     const Range rg = block_range(d.N, K);
     const long N = d.N;
     double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock)
+    for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock) {
+        double t[3];
+        row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.sh, act, t);
         for (int c = 0; c < 3; ++c) {
             if (!act[c]) continue;
-            const double t = row_apply<double>(d, i, d.mdiag, d.upper, d.lower, d.sh + c * N);
-            d.qt[c * N + i] = t;
-            acc[c] += t * t;
-            acc[3 + c] += t * d.pt[c * N + i];
+            acc[c] += t[c] * t[c];
+            acc[3 + c] += t[c] * d.pt[c * N + i];
+            d.qt[c * N + i] = t[c];
         }
+    }
     __shared__ double tot[6];
     if (reduce_last<6>(acc, d, K, tot) && threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) {
@@ -2302,10 +2384,12 @@ __global__ void __launch_bounds__(kBlock) k_mx_resid(Batch bt)
     const long N = d.N;
     double v[3] = {0, 0, 0};
     for (int i = rg.beg + threadIdx.x; i < rg.end; i += kBlock) {
+        double ax[3];
+        row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.U, act, ax);
         for (int c = 0; c < 3; ++c) {
             if (!act[c]) continue;
             const long j = c * N + i;
-            const double r = d.rhs[j] - row_apply<double>(d, i, d.mdiag, d.upper, d.lower, d.U + c * N);
+            const double r = d.rhs[j] - ax[c];
             d.r[j] = r;
             v[c] += fabs(r);
         }
@@ -2382,7 +2466,7 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
 // status over the steps, done: steps completed, first: 1 when a step failed
 // and was rolled back).  Scope (the host checks it): orthogonal meshes, at
 // most 4 pressure correctors without non-orthogonal correction, Jacobi CG
-// and BiCG, FP64 or mixed precision.
+// and BiCG, at most 6 neighbours per cell, mixed precision.
 // ---------------------------------------------------------------------------
 constexpr int kSolo = 512;
 constexpr int kSoloWaves = kSolo / 64;
@@ -2436,8 +2520,11 @@ __device__ void solo_bicg_init(const DevCase &d, SoloShared &sh)
     SOLO_FOR(i, d.N) {
         const double a1 = row_sum(d, i, d.mdiag, d.upper, d.lower);
         const double dg = d.mdiag[i];
+        const int every[3] = {1, 1, 1};
+        double ax3[3];
+        row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.U, every, ax3);
         for (int c = 0; c < 3; ++c) {
-            const double ax = row_apply<double>(d, i, d.mdiag, d.upper, d.lower, d.U + c * N);
+            const double ax = ax3[c];
             const double b = d.rhs[c * N + i];
             const double r = b - ax;
             d.r[c * N + i] = r;
@@ -2501,14 +2588,13 @@ __device__ void solo_bicg_iterate(const DevCase &d, SoloShared &sh, const BiArr<
         // products (k_bicg_spmv)
         double acc[3] = {0.0, 0.0, 0.0};
         SOLO_FOR(i, d.N) {
+            T q[3], qt[3];
+            row_apply3_both<T>(d, i, v.diag, v.up, v.lo, v.p, v.pt, act, q, qt);
             for (int c = 0; c < 3; ++c) {
                 if (!act[c]) continue;
-                const T *p = v.p + c * N, *pt = v.pt + c * N;
-                const T q = row_apply<T>(d, i, v.diag, v.up, v.lo, p);
-                const T qt = row_apply<T>(d, i, v.diag, v.lo, v.up, pt);
-                v.q[c * N + i] = q;
-                v.qt[c * N + i] = qt;
-                acc[c] += (double)pt[i] * (double)q;
+                acc[c] += (double)v.pt[c * N + i] * (double)q[c];
+                v.q[c * N + i] = q[c];
+                v.qt[c * N + i] = qt[c];
             }
         }
         solo_sum<3>(acc, sh);
@@ -2565,17 +2651,13 @@ __device__ void solo_bicg_iterate(const DevCase &d, SoloShared &sh, const BiArr<
     __syncthreads();
 }
 
-// momentum solve: FP64 BiCG, or FP64 refinement around restarted FP32 BiCG
-__device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
+// momentum solve: FP64 refinement around restarted FP32 BiCG
+__device__ void solo_momentum(const DevCase &d, SoloShared &sh)
 {
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) solo_ctl(d, sh.ks[c], 0);
     __syncthreads();
     solo_bicg_init(d, sh);
-    if (!mixed) {
-        solo_bicg_iterate<double>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
-        return;
-    }
     const long N = d.N;
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) solo_ctl(d, sh.ks[4 + c], 3);
@@ -2640,14 +2722,17 @@ __device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
                 if (keep[c]) d.U[(long)c * N + i] += (double)d.f_x[(long)c * N + i] / sc[c];
         __syncthreads();
         double w[3] = {0, 0, 0};
-        SOLO_FOR(i, d.N)
+        SOLO_FOR(i, d.N) {
+            double ax[3];
+            row_apply3<double>(d, i, d.mdiag, d.upper, d.lower, d.U, act, ax);
             for (int c = 0; c < 3; ++c) {
                 if (!act[c]) continue;
                 const long j = c * N + i;
-                const double r = d.rhs[j] - row_apply<double>(d, i, d.mdiag, d.upper, d.lower, d.U + c * N);
+                const double r = d.rhs[j] - ax[c];
                 d.r[j] = r;
                 w[c] += fabs(r);
             }
+        }
         solo_sum<3>(w, sh);
         if (threadIdx.x == 0)
             for (int c = 0; c < 3; ++c) {
@@ -2695,135 +2780,193 @@ __device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
     solo_bicg_iterate<double>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
 }
 
-// ---- pressure: Jacobi CG (k_cg_*, k_pcg_init; mixed: k_rr_*) -----------
+// ---- pressure: mixed-precision Jacobi CG (k_cg_*, k_rr_*) ---------------
 
-template <class T>
-__device__ __forceinline__ Row<T> solo_spmv_row(const DevCase &d, const CGArr<T> &v, int i)
+// rows of the product a thread takes at once
+constexpr int kSoloU = 8;
+
+// what the product below reads
+struct SoloCg {
+    float *lp;          // p of the whole case, in LDS
+    const float *val;   // sliced-ELL coefficients
+    const int32_t *mode, *off, *col;
+    int N, W;
+};
+
+// row i = tid + 512 c of the product in difference form, as spmv_row<float>
+// forms it: p from LDS, the row's own coefficients (the mirrored ones have
+// the same values).  Slots past W read slot W - 1 and count nothing.
+__device__ __forceinline__ float solo_row(const SoloCg &g, const float *__restrict__ exc, int i, float pf)
 {
-    const SellView sw = sell_view(d);
-    return d.sell_W == 6 ? spmv_row<T, 6>(sw, v, i / kBlock, i) : spmv_row<T, 0>(sw, v, i / kBlock, i);
+    typedef const __attribute__((address_space(4))) int cint;
+    const int sl = __builtin_amdgcn_readfirstlane(i / kBlock);
+    const int mode = ((cint *)g.mode)[sl];
+    const size_t base = (size_t)sl * g.W * kBlock + (i & (kBlock - 1));
+    const auto *__restrict__ val = gmem(g.val + base);
+    float a[6], pj[6];
+    if (mode != 1) {
+        cint *off = (cint *)(g.off + (size_t)sl * g.W);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int kk = min(k, g.W - 1);
+            a[k] = val[(size_t)kk * kBlock];
+            pj[k] = g.lp[min(max(i + off[kk], 0), g.N - 1)];
+        }
+    } else {
+        const auto *__restrict__ col = gmem(g.col + base);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int kk = min(k, g.W - 1);
+            a[k] = val[(size_t)kk * kBlock];
+            pj[k] = g.lp[col[(size_t)kk * kBlock]];
+        }
+    }
+    double qa = 0.0, so = 0.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const double ak = k < g.W ? (double)a[k] : 0.0;
+        qa += ak * (double)pj[k];
+        so += ak;
+    }
+    const double ex = mode != 2 ? (double)gmem(exc)[i] : 0.0;
+    return (float)(qa + (ex - so) * (double)pf);
 }
 
-// Cells per thread per round of the whole-step kernel's CG passes: a round
-// issues the loads of all its cells before the first store (the arrays are
-// not known to be distinct, so a store keeps later loads behind it, and one
-// cell at a time would pay a memory round trip per cell).  A thread still
-// takes cells i = tid, tid + kSolo, ... in that order, so the sums are
-// formed as before.
-constexpr int kSoloU = 4;
+__device__ bool solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s);
 
-// one FP64 or FP32 CG iteration on state s (dir, product, update of the
-// launched kernels); mixed: the FP32 recurrence with the FP64 solution
-template <class T>
-__device__ void solo_cg_iteration(const DevCase &d, SoloShared &sh, const CGArr<T> &v, KState &s)
+// The FP32 recurrence of one case in one workgroup, its vectors on the chip:
+// p of all cells in LDS (128 KB at the largest size), r and z of a thread's
+// C cells i = tid, tid + 512, ... in registers; x (FP64), q, the diagonal
+// and the coefficients come from the L2.  With the vectors in memory
+// an iteration of 30^3 cells took 82 us: three passes of 14 to 27 rounds,
+// each a memory round trip; now 49 us, of which the product takes 25 (one
+// CU's conversions, FP64 sums and LDS gathers).  Every sum is formed as before (a thread's cells
+// in order, the wave, the waves in order): the results are the same bits.
+template <int C>
+__device__ void solo_rr(const DevCase &d, SoloShared &sh, KState &s, float *lp)
 {
-    constexpr bool kMixed = sizeof(T) == 4;
-    const bool first = s.first;
-    const T beta = (T)s.beta;
     const int N = d.N;
-    for (int b = (int)threadIdx.x; b < N; b += kSolo * kSoloU) {
-        T rv[kSoloU], dv[kSoloU], pv[kSoloU];
+    int tid = (int)threadIdx.x;
+    const SoloCg g{lp, d.f_sell_val, d.sell_mode, d.sell_off, d.sell_col, N, d.sell_W};
+    const float *exc = d.f_pexc;
+    auto *__restrict__ x = gmem(d.p);
+    auto *__restrict__ rg = gmem(d.f_r);
+    const auto *__restrict__ dg = gmem((const float *)d.f_pdiag);
+    auto *__restrict__ qg = gmem(d.f_q);
+    float r[C], z[C];
+    auto load_r = [&] {
+        asm volatile("" : "+v"(tid));
 #pragma unroll
-        for (int u = 0; u < kSoloU; ++u) {
-            const int i = b + u * kSolo;
+        for (int c = 0; c < C; ++c) {
+            const int i = tid + c * kSolo;
             if (i < N) {
-                rv[u] = v.r[i];
-                dv[u] = v.diag[i];
-                pv[u] = first ? (T)0 : v.p[i];
+                r[c] = rg[i];
+                z[c] = r[c] / dg[i];
             }
         }
+    };
 #pragma unroll
-        for (int u = 0; u < kSoloU; ++u) {
-            const int i = b + u * kSolo;
-            if (i < N) {
-                const T z = rv[u] / dv[u];
-                v.p[i] = first ? z : z + beta * pv[u];
+    for (int c = 0; c < C; ++c) r[c] = z[c] = 0.0f;
+    load_r();
+    // iterations with a replacement check after every fourth, as the
+    // launched driver enqueues them (a paused recurrence waits for it)
+    constexpr int kReplaceEvery = 4;
+    const long limit = ((long)d.p_max_iter + 2) * kReplaceEvery;
+    for (long k = 0; k < limit && s.done != 1; ++k) {
+        if (!s.done) {
+            const bool first = s.first;
+            const float beta = (float)s.beta;
+            asm volatile("" : "+v"(tid));   // C addresses are formed where they are used, not kept from before the loop
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int i = tid + c * kSolo;
+                if (i < N) lp[i] = first ? z[c] : z[c] + beta * lp[i];
+            }
+            __syncthreads();
+            asm volatile("" : "+v"(tid));
+            double pq[1] = {0.0};
+            for (int i0 = tid; i0 < N; i0 += kSolo * kSoloU) {
+                float pf[kSoloU], q[kSoloU];
+#pragma unroll
+                for (int u = 0; u < kSoloU; ++u) {
+                    const int i = i0 + u * kSolo;
+                    if (i < N) {
+                        pf[u] = lp[i];
+                        q[u] = solo_row(g, exc, i, pf[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kSoloU; ++u) {
+                    const int i = i0 + u * kSolo;
+                    if (i < N) {
+                        qg[i] = q[u];
+                        pq[0] += (double)pf[u] * (double)q[u];
+                    }
+                }
+            }
+            solo_sum<1>(pq, sh);
+            if (tid == 0) {
+                if (!(pq[0] > 0.0) || !isfinite(pq[0])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
+                else s.alpha = s.rho / pq[0];
+            }
+            __syncthreads();
+            if (!s.done) {
+                const double al = s.alpha;
+                const float alf = (float)al;
+                asm volatile("" : "+v"(tid));
+                double acc[2] = {0.0, 0.0};
+                // in rounds of 8 cells: their loads are issued together
+#pragma unroll
+                for (int b = 0; b < C / 8; ++b) {
+                    double xv[8];
+                    float qv[8], dv[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int i = tid + (8 * b + j) * kSolo;
+                        if (i < N) {
+                            xv[j] = x[i];
+                            qv[j] = qg[i];
+                            dv[j] = dg[i];
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int c = 8 * b + j, i = tid + c * kSolo;
+                        if (i < N) {
+                            x[i] = xv[j] + al * (double)lp[i];
+                            r[c] = r[c] - alf * qv[j];
+                            z[c] = r[c] / dv[j];
+                            acc[0] += fabs((double)r[c]);
+                            acc[1] += (double)r[c] * (double)z[c];
+                        }
+                    }
+                }
+                solo_sum<2>(acc, sh);
+                if (tid == 0) {
+                    s.iters += 1;
+                    s.nres = acc[0] / s.nf;
+                    s.first = 0;
+                    s.xbar = s.rho;   // rho of the previous iteration (for a replacement)
+                    if (!isfinite(s.nres)) set_done(s, FVM_ENUMERIC);
+                    else if (s.nres <= s.tol_eff || s.iters >= s.max_iter) s.done = 2;   // verify on the true residual
+                    else if (!(acc[1] > 0.0) || !isfinite(acc[1])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
+                    else {
+                        s.beta = acc[1] / s.rho;
+                        s.rho = acc[1];
+                    }
+                }
+                __syncthreads();
             }
         }
+        if ((k + 1) % kReplaceEvery == 0 && solo_rr_replace(d, sh, s)) load_r();
     }
-    __syncthreads();
-    double pq[1] = {0.0};
-    for (int b = (int)threadIdx.x; b < N; b += kSolo * 2) {
-        Row<T> rw[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int i = b + u * kSolo;
-            if (i < N) rw[u] = solo_spmv_row<T>(d, v, i);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int i = b + u * kSolo;
-            if (i < N) {
-                v.q[i] = rw[u].q;
-                pq[0] += rw[u].pq;
-            }
-        }
-    }
-    solo_sum<1>(pq, sh);
-    if (threadIdx.x == 0) {
-        if (!(pq[0] > 0.0) || !isfinite(pq[0])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
-        else s.alpha = s.rho / pq[0];
-    }
-    __syncthreads();
-    if (s.done) return;
-    const double al = s.alpha;
-    double acc[2] = {0.0, 0.0};
-    for (int b = (int)threadIdx.x; b < N; b += kSolo * kSoloU) {
-        double xv[kSoloU];
-        T pv[kSoloU], rv[kSoloU], qv[kSoloU], dv[kSoloU];
-#pragma unroll
-        for (int u = 0; u < kSoloU; ++u) {
-            const int i = b + u * kSolo;
-            if (i < N) {
-                xv[u] = d.p[i];
-                pv[u] = v.p[i];
-                rv[u] = v.r[i];
-                qv[u] = v.q[i];
-                dv[u] = v.diag[i];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kSoloU; ++u) {
-            const int i = b + u * kSolo;
-            if (i >= N) continue;
-            d.p[i] = xv[u] + al * (double)pv[u];
-            if (!kMixed) {
-                const double r = (double)rv[u] - al * (double)qv[u];
-                v.r[i] = (T)r;
-                acc[0] += fabs(r);
-                acc[1] += r * (r / (double)dv[u]);
-            } else {
-                const float ri = (float)rv[u] - (float)al * (float)qv[u];
-                v.r[i] = (T)ri;
-                acc[0] += fabs((double)ri);
-                acc[1] += (double)ri * (double)(ri / (float)dv[u]);
-            }
-        }
-    }
-    solo_sum<2>(acc, sh);
-    if (threadIdx.x == 0) {
-        s.iters += 1;
-        s.nres = acc[0] / s.nf;
-        s.first = 0;
-        if (kMixed) s.xbar = s.rho;   // rho of the previous iteration (for a replacement)
-        if (!isfinite(s.nres)) set_done(s, FVM_ENUMERIC);
-        else if (kMixed && (s.nres <= s.tol_eff || s.iters >= s.max_iter)) s.done = 2;   // verify on the true residual
-        else if (!kMixed && s.nres <= s.tol_eff) set_done(s, FVM_OK);
-        else if (!kMixed && s.iters >= s.max_iter) set_done(s, FVM_WARN_MAXITER);
-        else if (!(acc[1] > 0.0) || !isfinite(acc[1])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
-        else {
-            s.beta = acc[1] / s.rho;
-            s.rho = acc[1];
-        }
-    }
-    __syncthreads();
 }
 
-// mixed precision: residual replacement (k_rr_replace)
-__device__ void solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s)
+// residual replacement (k_rr_replace); whether one was made
+__device__ bool solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s)
 {
-    if (s.done == 1) return;
-    if (s.done == 0 && !(s.nres < 0.1 * s.scale)) return;
+    if (s.done == 1) return false;
+    if (s.done == 0 && !(s.nres < 0.1 * s.scale)) return false;
     double acc[2] = {0.0, 0.0};
     SOLO_FOR(i, d.N) {
         const double r = d.pb[i] - row_apply<double>(d, i, d.pdiag, d.poff, d.poff, d.p);
@@ -2848,29 +2991,25 @@ __device__ void solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s)
         }
     }
     __syncthreads();
+    return true;
 }
 
 // pressure solve of the assembled system (pdiag, poff, pb), x = p
-__device__ void solo_pressure(const DevCase &d, SoloShared &sh, bool mixed)
+__device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp)
 {
     KState &s = sh.ks[3];
     if (threadIdx.x == 0) solo_ctl(d, s, 1);
-    // sliced-ELL values (k_sell_fill) and, mixed, the FP32 copies (k_mx_cvt)
+    // sliced-ELL values (k_sell_fill) and the FP32 copies (k_mx_cvt)
     const int nsl = (d.N + kBlock - 1) / kBlock;
     SOLO_FOR(e, nsl * d.sell_W * kBlock) {
         const int fe = d.sell_fe[e];
         const double a = fe < 0 ? 0.0 : d.poff[fe >> 1];
-        if (mixed) d.f_sell_val[e] = (float)a;
-        else d.sell_val[e] = a;
+        d.f_sell_val[e] = (float)a;
     }
-    if (mixed)
-        SOLO_FOR(t, d.N > d.Fi ? d.N : d.Fi) {
-            if (t < d.N) {
-                d.f_pdiag[t] = (float)d.pdiag[t];
-                d.f_pexc[t] = (float)row_sum(d, t, d.pdiag, d.poff, d.poff);
-            }
-            if (t < d.Fi) d.f_poff[t] = (float)d.poff[t];
-        }
+    SOLO_FOR(t, d.N) {
+        d.f_pdiag[t] = (float)d.pdiag[t];
+        d.f_pexc[t] = (float)row_sum(d, t, d.pdiag, d.poff, d.poff);
+    }
     // start (k_pcg_sumx, k_pcg_init with Jacobi)
     double xb[1] = {0.0};
     SOLO_FOR(i, d.N) xb[0] += d.p[i];
@@ -2905,36 +3044,26 @@ __device__ void solo_pressure(const DevCase &d, SoloShared &sh, bool mixed)
         else s.rho = v[2];
     }
     __syncthreads();
-    if (!mixed) {
-        const CGArr<double> a = cg_arrays<double>(d, 0);
-        for (long it = 0; it <= (long)d.p_max_iter && !s.done; ++it) solo_cg_iteration<double>(d, sh, a, s);
-    } else {
-        // k_rr_start: r32 = r64, rho = r32.(r32/diag32)
-        if (!s.done) {
-            double rho[1] = {0.0};
-            SOLO_FOR(i, d.N) {
-                const float r = (float)d.r[i];
-                d.f_r[i] = r;
-                rho[0] += (double)r * (double)(r / d.f_pdiag[i]);
-            }
-            solo_sum<1>(rho, sh);
-            if (threadIdx.x == 0) {
-                s.scale = s.nres;
-                if (!(rho[0] > 0.0) || !isfinite(rho[0])) { set_done(s, FVM_ENUMERIC); s.iters = 1; }
-                else s.rho = rho[0];
-            }
-            __syncthreads();
+    // k_rr_start: r32 = r64, rho = r32.(r32/diag32)
+    if (!s.done) {
+        double rho[1] = {0.0};
+        SOLO_FOR(i, d.N) {
+            const float r = (float)d.r[i];
+            d.f_r[i] = r;
+            rho[0] += (double)r * (double)(r / d.f_pdiag[i]);
         }
-        // iterations with a replacement check after every fourth, as the
-        // launched driver enqueues them (a paused recurrence waits for it)
-        constexpr int kReplaceEvery = 4;
-        const CGArr<float> a = cg_arrays<float>(d, 0);
-        const long limit = ((long)d.p_max_iter + 2) * kReplaceEvery;
-        for (long k = 0; k < limit && s.done != 1; ++k) {
-            if (!s.done) solo_cg_iteration<float>(d, sh, a, s);
-            if ((k + 1) % kReplaceEvery == 0) solo_rr_replace(d, sh, s);
+        solo_sum<1>(rho, sh);
+        if (threadIdx.x == 0) {
+            s.scale = s.nres;
+            if (!(rho[0] > 0.0) || !isfinite(rho[0])) { set_done(s, FVM_ENUMERIC); s.iters = 1; }
+            else s.rho = rho[0];
         }
+        __syncthreads();
     }
+    if (d.N <= 8 * kSolo) solo_rr<8>(d, sh, s, lp);
+    else if (d.N <= 16 * kSolo) solo_rr<16>(d, sh, s, lp);
+    else if (d.N <= 32 * kSolo) solo_rr<32>(d, sh, s, lp);
+    else solo_rr<64>(d, sh, s, lp);
     if (threadIdx.x == 0 && s.done != 1) set_done(s, FVM_ENUMERIC);
     __syncthreads();
 }
@@ -2950,6 +3079,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
 {
     __shared__ SoloShared sh;
     __shared__ DevCase sdc;
+    extern __shared__ __align__(16) float solo_p[];
     if ((int)blockIdx.x >= bt.n) return;
     // the case descriptor in LDS: the step reads its fields after its own
     // stores throughout (the descriptor's memory could alias them), and from
@@ -2962,7 +3092,6 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
         __syncthreads();
     }
     const DevCase &d = sdc;
-    const bool mixed = d.f_x != nullptr;
     const long N = d.N, F = d.F;
     int32_t worst = FVM_OK;
     int steps_done = 0, failed = 0, np = 0;
@@ -2979,7 +3108,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
         __syncthreads();
         SOLO_FOR(i, d.N) el_mom_cell(d, i, 0);
         __syncthreads();
-        solo_momentum(d, sh, mixed);
+        solo_momentum(d, sh);
         int32_t st = FVM_OK;
         for (int c = 0; c < 3; ++c) worst_status(st, sh.ks[c].status);
         if (threadIdx.x == 0)
@@ -2993,7 +3122,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
                 __syncthreads();
                 SOLO_FOR(i, d.N) el_p_cell(d, i, 1);
                 __syncthreads();
-                solo_pressure(d, sh, mixed);
+                solo_pressure(d, sh, solo_p);
                 if (threadIdx.x == 0) sh.rec[3 + np] = sh.ks[3];
                 ++np;
                 worst_status(st, sh.ks[3].status);
@@ -4082,7 +4211,12 @@ void launch_solo_piso(const BatchSet &bs, int n_steps, int n_corr, hipStream_t s
 {
     Prof p("solo_piso", s);
     const Batch &b = bs.b[SZ_CELL];
-    hipLaunchKernelGGL(k_solo_piso, dim3((unsigned)b.n), dim3(kSolo), 0, s, b, n_steps, n_corr);
+    int cells = 0;
+    for (int c = 0; c < bs.n; ++c) cells = std::max(cells, bs.host[c]->N);
+    const size_t lds = sizeof(float) * (size_t)cells;
+    (void)hipFuncSetAttribute((const void *)k_solo_piso, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(sizeof(float) * kSoloMaxCells));
+    hipLaunchKernelGGL(k_solo_piso, dim3((unsigned)b.n), dim3(kSolo), lds, s, b, n_steps, n_corr);
 }
 void launch_mx_inner_init(const BatchSet &bs, int, hipStream_t s) { run(k_mx_inner_init, bs, SZ_CELL, s); }
 void launch_mx_inner_iter(const BatchSet &bs, int, hipStream_t s)
