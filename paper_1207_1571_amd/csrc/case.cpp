@@ -281,15 +281,19 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
         d.hy_w = b.take<double>(E); d.hy_dl = b.take<double>(E); d.hy_g = b.take<double>(E); d.hy_phi = b.take<double>(E);
     }
     {
-        const PartsHost &P = mesh_parts(m);
-        d.res_G = P.G; d.res_W = P.W; d.res_n = P.n_max; d.res_local = P.local_max;
+        const PartsHost &P = mixed ? mesh_tile_parts(m) : mesh_parts(m);
+        d.res_G = P.G; d.res_W = P.W; d.res_n = P.n_max; d.res_local = P.local_max; d.res_halo_max = P.halo_max;
         if (P.G > 0) {
             d.res_start = b.take<int32_t>(P.start.size()); d.res_hstart = b.take<int32_t>(P.hstart.size());
-            d.res_far = b.take<int32_t>(P.far.size()); d.res_shown = b.take<int32_t>(P.shown.size());
+            if (mixed) d.res_pub = b.take<uint8_t>(N);
+            else { d.res_far = b.take<int32_t>(P.far.size()); d.res_shown = b.take<int32_t>(P.shown.size()); }
             d.res_fin = b.take<int32_t>(P.G);
             d.res_cell = b.take<int32_t>(N); d.res_fe = b.take<int32_t>(P.fe.size());
             d.res_idx = b.take<uint16_t>(P.idx.size()); d.res_halo = b.take<int32_t>(P.halo.size());
-            d.res_slots = b.take<double>(kResSlotWords);
+            // a part by itself reduces without slots
+            d.res_words = (int32_t)(kResGens * (mixed ? rr_gen_words((P.G + kRrGroup - 1) / kRrGroup)
+                                                      : P.G > 1 ? res_gen_words(res_groups(P.G)) : 0));
+            d.res_slots = b.take<double>(d.res_words);
             d.res_gen = b.take<int32_t>(1);
         }
     }
@@ -573,10 +577,10 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     UPCHK(up(d.sell_off, m->sell_off, s)); UPCHK(up(d.sell_mir, m->sell_mir, s));
     UPCHK(up(d.sell_fe, m->sell_fe, s)); UPCHK(up(d.sell_col, m->sell_col, s));
     if (d.res_G > 0) {
-        const PartsHost &P = mesh_parts(*m);
+        const PartsHost &P = o->precision == FVM_MIXED ? mesh_tile_parts(*m) : mesh_parts(*m);
         UPCHK(up(d.res_start, P.start, s)); UPCHK(up(d.res_hstart, P.hstart, s)); UPCHK(up(d.res_cell, P.cell, s));
         UPCHK(up(d.res_fe, P.fe, s)); UPCHK(up(d.res_idx, P.idx, s)); UPCHK(up(d.res_halo, P.halo, s));
-        UPCHK(up(d.res_far, P.far, s)); UPCHK(up(d.res_shown, P.shown, s));
+        UPCHK(up(d.res_far, P.far, s)); UPCHK(up(d.res_shown, P.shown, s)); UPCHK(up(d.res_pub, P.pub, s));
     }
     if (d.amg_nl > 0) {
         const AmgHost &A = mesh_amg(*m);
@@ -900,12 +904,16 @@ struct ResidentBatch {
     // false when the case's groups do not fit beside what is there
     bool add(const DevCase *self, const DevCase &d)
     {
-        const int G = d.res_G, ng = res_groups(G);
+        const int G = d.res_G;
+        const bool mixed = d.f_x != nullptr;
         if (bs.n > 0 && bs.host[0]->res_W != d.res_W) return false;
-        int at[kResGroups], sum[kResGroups];
+        auto group = [&](int part) { return mixed ? part / kRrGroup : res_group_of(part, G); };
+        int at[kRrGroups], sum[kResGroups];
         std::copy(fill, fill + kResGroups, sum);
-        for (int g = 0; g < ng; ++g) {
-            const int size = res_group_first(g + 1, G) - res_group_first(g, G);
+        for (int part = 0; part < G;) {
+            const int g = group(part);
+            int size = 0;
+            while (part < G && group(part) == g) ++part, ++size;
             at[g] = -1;
             // the fullest XCD that still has room
             for (int x = 0; x < kResGroups; ++x)
@@ -914,7 +922,7 @@ struct ResidentBatch {
             sum[at[g]] += size;
         }
         for (int part = 0; part < G; ++part) {
-            const int x = at[res_group_of(part, G)], b = kResGroups * fill[x]++ + x;
+            const int x = at[group(part)], b = kResGroups * fill[x]++ + x;
             cs[b] = (uint8_t)bs.n;
             pt[b] = (uint8_t)part;
         }
@@ -932,7 +940,8 @@ fvm_status resident_launch(ResidentBatch &rb, const fvm_solver_ctl *ctl, int ser
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
-    launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
+    if (rb.bs.host[0]->f_x) launch_res_rr(rb.bs, rb.cs, rb.pt, t_res_ticks, serial, s);
+    else launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
     HIPCHK(hipGetLastError());
     HIPCHK(hipEventRecord(R->last, s));
     R->any = true;
@@ -974,11 +983,19 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
 {
     const int precond = ctl_src == 2 ? ctl->precond : g.cs[0]->o.p_ctl.precond;
     std::vector<int> on;
-    if (kind == 1 && precond == FVM_PC_JACOBI && g.cs[0]->o.precision == FVM_FP64 && resident_usable())
+    if (kind == 1 && precond == FVM_PC_JACOBI && resident_usable())
         for (int i = 0; i < g.n(); ++i)
             if (g.cs[i]->d.res_G > 0) on.push_back(i);
     if (on.empty()) return run_launched(g, kind, ctl_src, ctl, res);
     const int serial = resident_serial();
+    if (g.cs[0]->o.precision == FVM_MIXED) {
+        // the recurrence starts from the launched solve's start
+        BatchSet bs;
+        bs.n = 0;
+        for (int i : on) batch_add(bs, g.cs[i]->d.self, &g.cs[i]->d);
+        launch_set_ctl(bs, 3, 1, ctl_src, ctl ? ctl->tol : 0.0, ctl ? ctl->rel_tol : 0.0, ctl ? ctl->max_iter : 0, g.s);
+        launch_rr_resident_start(bs, g.s);
+    }
     fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial);
     if (st != FVM_OK) return st;
     if ((int)on.size() < g.n()) {
@@ -1367,7 +1384,7 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
     unsigned char *gt = take(sizeof(unsigned int) * (size_t)d.red_stride2);
     unsigned char *tk = take(sizeof(unsigned int) * 64);
     unsigned char *ks = take(sizeof(KState) * kNumKs);
-    unsigned char *rs = d.res_G > 0 ? take(sizeof(double) * kResSlotWords) : nullptr;
+    unsigned char *rs = d.res_G > 0 ? take(sizeof(double) * (size_t)std::max(1, d.res_words)) : nullptr;
     unsigned char *rg = d.res_G > 0 ? take(sizeof(int32_t)) : nullptr;
     if (h) {
         h->res_slots = reinterpret_cast<double *>(rs);

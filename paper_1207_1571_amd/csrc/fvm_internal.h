@@ -25,6 +25,7 @@ constexpr int kAmgTailLds = 64 * 1024;   // LDS bytes of the fused smallest-leve
 // than 6 neighbours per cell, halos larger than the LDS)
 struct PartsHost;
 const PartsHost &mesh_parts(const fvm_mesh &m);
+const PartsHost &mesh_tile_parts(const fvm_mesh &m);   // parts in the cells' order (resident_rr.h)
 constexpr int kResCells = 4096;       // largest part (512 threads of 8 cells)
 constexpr int kResParts = 256;        // most parts of a case: one workgroup per CU
 constexpr int kResGroup = 32;         // parts of a group: the CUs of an XCD
@@ -32,12 +33,21 @@ constexpr int kResGroups = kResParts / kResGroup;
 constexpr int kResLocal = 7680;       // own cells and halo of a part: 12 bytes of LDS for each, 16 per own cell
 constexpr int kResGens = 4;           // generations of reduction slots
 constexpr int kResMaxSum = 4;         // sums per reduction (slots laid out)
-constexpr size_t kResSlotWords = (size_t)kResGens * kResMaxSum * kResGroups * (kResGroup + kResGroups);
 #ifdef __HIPCC__
 #define RES_HD __host__ __device__
 #else
 #define RES_HD
 #endif
+// words of a generation of slots: the parts' own sums, then the group sums,
+// a copy for each reading group
+RES_HD inline size_t res_gen_words(int ngrp) { return (size_t)kResMaxSum * (ngrp * kResGroup + kResGroups * kResGroups); }
+// the same for the mixed-precision solve (resident_rr.h): parts of four
+// tiles of 1024 cells in order, groups of 16 parts (64 tiles), two sums
+constexpr int kRrTile = 1024;
+constexpr int kRrGroup = 16;
+constexpr int kRrGroups = kResParts / kRrGroup;
+constexpr int kRrLds = 152 * 1024;    // p of own cells and halo (FP32) and the halo's positions
+RES_HD inline size_t rr_gen_words(int ngrp) { return (size_t)2 * (ngrp * 64 + kRrGroups * kRrGroups); }
 // the G parts of a case in groups of nearly equal size: their number, the
 // group of a part, and a group's first part
 RES_HD inline int res_groups(int G) { return (G + kResGroup - 1) / kResGroup; }
@@ -100,9 +110,10 @@ struct AmgHost {
 // in the part's local vector (own cells, then the halo).  halo[hstart[p] ..]
 // lists the positions of the part's neighbours in other parts, ascending.
 struct PartsHost {
-    int32_t G = 0, W = 0, n_max = 0, local_max = 0;
+    int32_t G = 0, W = 0, n_max = 0, local_max = 0, halo_max = 0;
     std::vector<int32_t> start, hstart, far, shown, cell, fe, halo;
     std::vector<uint16_t> idx;
+    std::vector<uint8_t> pub;   // tile parts: 1 = in the halo of a part of the group, 2 = of another group
 };
 
 struct fvm_mesh {
@@ -158,7 +169,7 @@ struct fvm_mesh {
     // slots mirrored from the upper ones, every neighbour inside the mesh
     int32_t sell_n7 = 0;
     mutable std::shared_ptr<AmgHost> amg;   // AMG hierarchy, built on first use
-    mutable std::shared_ptr<PartsHost> parts;   // parts of the resident CG, built on first use
+    mutable std::shared_ptr<PartsHost> parts, tile_parts;   // parts of the resident CG, built on first use
 };
 
 // ---------------------------------------------------------------------------
@@ -283,9 +294,10 @@ struct DevCase {
     // reduction slots (kResSlotWords) and the generation the next solve
     // starts with, the last solve each part finished; a solve whose waits ran out sets
     // ks[kNumKs - 1].pad[0]
-    int32_t res_G, res_W, res_n, res_local;
+    int32_t res_G, res_W, res_n, res_local, res_halo_max, res_words;
     int32_t *res_start, *res_hstart, *res_far, *res_shown, *res_fin, *res_cell, *res_fe, *res_halo;
     uint16_t *res_idx;
+    uint8_t *res_pub;
     double *res_slots;
     int32_t *res_gen;
     // reductions
@@ -408,6 +420,10 @@ void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, con
                    int serial, hipStream_t s);
 void launch_res_reset(const BatchSet &bs, int serial, hipStream_t s);
 int res_prepare();
+// the mixed-precision solve: start (residual, FP32 copies, first rho) and the
+// resident recurrence
+void launch_rr_resident_start(const BatchSet &bs, hipStream_t s);
+void launch_res_rr(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, long ticks, int serial, hipStream_t s);
 // whole PISO steps, one workgroup per case (small orthogonal Jacobi/BiCG
 // cases, n_corr <= kSoloMaxCorr): grid = the batch's cases; the last
 // step's record is left in each case's Krylov state slots (see

@@ -2447,6 +2447,7 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
 }
 
 #include "resident_cg.h"
+#include "resident_rr.h"
 
 // ---------------------------------------------------------------------------
 // Whole PISO steps of small cases, one workgroup per case
@@ -4181,7 +4182,39 @@ int res_prepare()
                 return 1;
             }
         }
+    for (const void *k : {(const void *)k_res_rr<4>, (const void *)k_res_rr<6>}) {
+        int blocks = 0;
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kRrLds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, kResThreads, kRrLds) != hipSuccess || blocks < 1) {
+            (void)hipGetLastError();
+            return 1;
+        }
+    }
     return 0;
+}
+
+void launch_rr_resident_start(const BatchSet &bs, hipStream_t s)
+{
+    run(k_pcg_sumx, bs, SZ_CELL, s);
+    run(k_pcg_init, bs, SZ_CELL, s, 0);
+    launch_rr_start(bs, s);
+}
+
+void launch_res_rr(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, long ticks, int serial, hipStream_t s)
+{
+    Prof p("pcg32_resident", s);
+    ResMap map;
+    int grid = 0;
+    size_t lds = 0;
+    for (int b = 0; b < kResParts; ++b) {
+        map.cs[b] = cs[b];
+        map.pt[b] = pt[b];
+        if (cs[b] != 255) grid = b + 1;
+    }
+    for (int c = 0; c < bs.n; ++c)
+        lds = std::max(lds, sizeof(float) * (size_t)bs.host[c]->res_local + sizeof(int32_t) * (size_t)bs.host[c]->res_halo_max);
+    hipLaunchKernelGGL(bs.host[0]->res_W == 4 ? k_res_rr<4> : k_res_rr<6>, dim3((unsigned)grid), dim3(kResThreads), lds, s,
+                       bs.b[SZ_CELL], map, serial, ticks);
 }
 
 void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,

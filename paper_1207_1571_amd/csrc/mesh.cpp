@@ -548,6 +548,58 @@ void bisect(PartCell *a, int32_t n, int32_t g, std::vector<int32_t> &size)
     bisect(a + nl, n - nl, g - gl, size);
 }
 
+// entries, local places and halos of the parts of h (start, cell set); false
+// when a part's own cells and halo exceed `limit`
+bool fill_parts(const fvm_mesh &m, PartsHost &h, const std::vector<int32_t> &part, const std::vector<int32_t> &pos,
+                int32_t W, int32_t limit)
+{
+    const int32_t N = m.N, G = (int32_t)h.start.size() - 1;
+    std::vector<int32_t> mark(N, -1), where(N), found;
+    h.fe.assign((size_t)W * N, -1);
+    h.idx.assign((size_t)W * N, 0);
+    for (int32_t p = 0; p < G; ++p) {
+        const int32_t p0 = h.start[p], n = h.start[p + 1] - h.start[p];
+        found.clear();
+        auto others = [&](int32_t j) {
+            if (part[j] != p && mark[j] != p) {
+                mark[j] = p;
+                found.push_back(pos[j]);
+            }
+        };
+        for (int32_t l = 0; l < n; ++l) {
+            const int32_t i = h.cell[p0 + l];
+            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k) others(m.own[m.losort[k]]);
+            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f) others(m.nei[f]);
+        }
+        std::sort(found.begin(), found.end());
+        const int32_t H = (int32_t)found.size();
+        if (n + H > limit) return false;
+        h.halo_max = std::max(h.halo_max, H);
+        h.n_max = std::max(h.n_max, n);
+        for (int32_t k = 0; k < H; ++k) where[found[k]] = n + k;
+        auto local = [&](int32_t j) { return part[j] == p ? pos[j] - p0 : where[pos[j]]; };
+        for (int32_t l = 0; l < n; ++l) {
+            const int32_t i = h.cell[p0 + l];
+            size_t e = (size_t)W * p0 + l;
+            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k, e += n) {
+                const int32_t f = m.losort[k];
+                h.fe[e] = 2 * f + 1;
+                h.idx[e] = (uint16_t)local(m.own[f]);
+            }
+            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f, e += n) {
+                h.fe[e] = 2 * f;
+                h.idx[e] = (uint16_t)local(m.nei[f]);
+            }
+        }
+        h.halo.insert(h.halo.end(), found.begin(), found.end());
+        h.hstart.push_back((int32_t)h.halo.size());
+        h.local_max = std::max(h.local_max, n + H);
+    }
+    h.G = G;
+    h.W = W;
+    return true;
+}
+
 }  // namespace
 
 const PartsHost &mesh_parts(const fvm_mesh &m)
@@ -565,7 +617,7 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
     for (int32_t i = 0; i < N; ++i) a[i] = PartCell{{m.C[i], m.C[(size_t)N + i], m.C[2 * (size_t)N + i]}, i};
     std::vector<int32_t> size;
     bisect(a.data(), N, G, size);
-    std::vector<int32_t> pos(N), part(N), mark(N, -1), where(N), found;
+    std::vector<int32_t> pos(N), part(N);
     h->start.assign(1, 0);
     h->hstart.assign(1, 0);
     h->cell.resize(N);
@@ -573,7 +625,6 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
         for (int32_t j = at; j < at + size[p]; ++j) part[a[j].i] = p;
         at += size[p];
         h->start.push_back(at);
-        h->n_max = std::max(h->n_max, size[p]);
     }
     // order inside a part: cells read from other groups, from other parts of
     // the group, the rest
@@ -605,51 +656,44 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
         }
     }
     a = std::vector<PartCell>();
-    h->fe.assign((size_t)W * N, -1);
-    h->idx.assign((size_t)W * N, 0);
-    for (int32_t p = 0; p < G; ++p) {
-        const int32_t p0 = h->start[p], n = size[p];
-        found.clear();
-        auto others = [&](int32_t j) {
-            if (part[j] != p && mark[j] != p) {
-                mark[j] = p;
-                found.push_back(pos[j]);
-            }
-        };
-        for (int32_t l = 0; l < h->shown[p]; ++l) {
-            const int32_t i = h->cell[p0 + l];
-            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k) others(m.own[m.losort[k]]);
-            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f) others(m.nei[f]);
-        }
-        std::sort(found.begin(), found.end());
-        const int32_t H = (int32_t)found.size();
-        if (n + H > kResLocal) {
-            *h = PartsHost();
-            m.parts = h;
-            return *h;
-        }
-        for (int32_t k = 0; k < H; ++k) where[found[k]] = n + k;
-        auto local = [&](int32_t j) { return part[j] == p ? pos[j] - p0 : where[pos[j]]; };
-        for (int32_t l = 0; l < n; ++l) {
-            const int32_t i = h->cell[p0 + l];
-            size_t e = (size_t)W * p0 + l;
-            for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k, e += n) {
-                const int32_t f = m.losort[k];
-                h->fe[e] = 2 * f + 1;
-                h->idx[e] = (uint16_t)local(m.own[f]);
-            }
-            for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f, e += n) {
-                h->fe[e] = 2 * f;
-                h->idx[e] = (uint16_t)local(m.nei[f]);
-            }
-        }
-        h->halo.insert(h->halo.end(), found.begin(), found.end());
-        h->hstart.push_back((int32_t)h->halo.size());
-        h->local_max = std::max(h->local_max, n + H);
-    }
-    h->G = G;
-    h->W = W;
+    if (!fill_parts(m, *h, part, pos, W, kResLocal)) *h = PartsHost();
     m.parts = h;
+    return *h;
+}
+
+
+const PartsHost &mesh_tile_parts(const fvm_mesh &m)
+{
+    if (m.tile_parts) return *m.tile_parts;
+    auto h = std::make_shared<PartsHost>();
+    const int32_t N = m.N, G = (N + kResCells - 1) / kResCells;
+    // the launched iterations' blocks must be the tiles (they are smaller on
+    // small meshes, where the block count is rounded up to a multiple of 8)
+    const int32_t blocks = ((N + 4 * kBlock - 1) / (4 * kBlock) + 7) / 8 * 8;
+    const int32_t per = ((N + blocks - 1) / blocks + kBlock - 1) / kBlock * kBlock;
+    if (G <= kResParts && m.sell_W <= 6 && per == kRrTile) {
+        std::vector<int32_t> part(N), pos(N);
+        h->cell.resize(N);
+        for (int32_t i = 0; i < N; ++i) {
+            pos[i] = h->cell[i] = i;
+            part[i] = i / kResCells;
+        }
+        h->start.resize(G + 1);
+        for (int32_t p = 0; p <= G; ++p) h->start[p] = std::min(N, p * kResCells);
+        h->hstart.assign(1, 0);
+        if (fill_parts(m, *h, part, pos, m.sell_W <= 4 ? 4 : 6, 65535) &&
+            4 * (int64_t)(h->local_max + h->halo_max) <= kRrLds) {
+            h->pub.assign(N, 0);
+            for (int32_t f = 0; f < m.Fi; ++f) {
+                const int32_t a = m.own[f], b = m.nei[f];
+                if (part[a] == part[b]) continue;
+                const uint8_t v = part[a] / kRrGroup == part[b] / kRrGroup ? 1 : 2;
+                h->pub[a] = std::max(h->pub[a], v);
+                h->pub[b] = std::max(h->pub[b], v);
+            }
+        } else *h = PartsHost();
+    }
+    m.tile_parts = h;
     return *h;
 }
 

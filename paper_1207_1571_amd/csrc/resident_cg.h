@@ -101,14 +101,13 @@ struct ResRed {
 // XCDs).  That is checked, not assumed: `local` is set once the group's
 // parts have all reported the same XCD, and only speeds up the stores.
 struct ResTeam {
-    double *slots;   // [kResGens]: own sums [kResMaxSum][kResGroups][kResGroup], then
+    double *slots;   // [kResGens]: own sums [kResMaxSum][ngrp][kResGroup], then
                      // group sums [kResMaxSum][reader's group][kResGroups]
     int part, G, gen;
     int grp, ngrp, first, size;   // group, groups, the group's first part and its parts
     bool local;
     long ticks;      // limit of one wait (100 MHz clock)
 };
-constexpr int kResGenWords = kResMaxSum * kResGroups * (kResGroup + kResGroups);
 
 // NV words at a + k * stride, polled by the wave until none is empty; false
 // when the time limit passes first.  Lanes past n read nothing and get 0.
@@ -174,9 +173,11 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
         return true;
     }
     if (wv == 0) {
-        double *own = tm.slots + (size_t)(tm.gen & (kResGens - 1)) * kResGenWords;
-        double *old = tm.slots + (size_t)((tm.gen - 1) & (kResGens - 1)) * kResGenWords;
-        double *all = own + kResMaxSum * kResGroups * kResGroup, *all_old = old + kResMaxSum * kResGroups * kResGroup;
+        const int S = tm.ngrp * kResGroup;   // own slots of a value
+        const size_t words = res_gen_words(tm.ngrp);
+        double *own = tm.slots + (tm.gen & (kResGens - 1)) * words;
+        double *old = tm.slots + ((tm.gen - 1) & (kResGens - 1)) * words;
+        double *all = own + kResMaxSum * S, *all_old = old + kResMaxSum * S;
         const int me = tm.grp * kResGroup + tm.part - tm.first;
         const bool one = tm.ngrp == 1, leads = tm.part == tm.first;
 #pragma unroll
@@ -184,12 +185,12 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
             double t = sh.part[par][k][0];
 #pragma unroll
             for (int w = 1; w < kResWaves; ++w) t += sh.part[par][k][w];
-            if (lane == 0) put_word(own + k * kResGroups * kResGroup + me, slot_word(t), tm.local);
+            if (lane == 0) put_word(own + k * S + me, slot_word(t), tm.local);
         }
         double t[NV];
         bool ok = true;
         if (one || leads) {
-            ok = poll_slots<NV>(own + tm.grp * kResGroup, kResGroups * kResGroup, tm.size, tm.ticks, t);
+            ok = poll_slots<NV>(own + tm.grp * kResGroup, S, tm.size, tm.ticks, t);
 #pragma unroll
             for (int k = 0; k < NV; ++k) t[k] = wave_total(t[k]);
             if (!one && ok && lane < tm.ngrp)
@@ -208,7 +209,7 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
             for (int k = 0; k < NV; ++k) t[k] = wave_total(t[k]);
         }
         // empty the previous generation's slots
-        if (lane < kResMaxSum) put_word(old + lane * kResGroups * kResGroup + me, kSentinel, tm.local);
+        if (lane < kResMaxSum) put_word(old + lane * S + me, kSentinel, tm.local);
         if (!one && leads)
             for (int e = lane; e < kResMaxSum * kResGroups; e += 64) gst(all_old + e * kResGroups + tm.grp, kSentinel);
         if (lane == 0) {
@@ -489,7 +490,7 @@ __global__ void k_res_reset(Batch bt, int serial)
     CASE_OF(bt);
     const long t = (long)K.raw * kBlock + threadIdx.x, stride = (long)K.G * kBlock;
     if (d.res_G > 0) {
-        for (long i = t; i < (long)kResGens * kResGenWords; i += stride) clear_word(d.res_slots, i);
+        for (long i = t; i < d.res_words; i += stride) clear_word(d.res_slots, i);
         if (t == 0) {
             *d.res_gen = 0;
             d.ks[kNumKs - 1].pad[0] = 0;

@@ -163,3 +163,55 @@ def test_a_wait_that_runs_out(static):
     st, info, p = once()      # and the next solve is resident again
     assert st == 1 and info["iters"] == 50
     assert np.linalg.norm(p - po) / np.linalg.norm(po) <= TOL
+
+
+def _hook():
+    from paper_1207_1571_amd import fvm
+    h = fvm.lib().fvm_resident_test_hook
+    h.argtypes, h.restype = [ct.c_long, ct.c_int], None
+    return h
+
+
+# mixed precision, tile parts: one group; two; sheet; RCM numbering (columns
+# explicit); a duct (fixed pressure); four groups
+@pytest.mark.parametrize("shape,numbering,kind", [
+    ((33, 33, 33), "lex", "cavity"), ((41, 47, 40), "lex", "duct"), ((230, 215, 1), "lex", "cavity"),
+    ((40, 40, 40), "rcm", "cavity"), ((64, 64, 63), "lex", "cavity")])
+def test_mixed_equals_the_launched_iterations(shape, numbering, kind):
+    """The resident FP32 recurrence gives the launched iterations' bits (the
+    launched side is reached by a launch whose wait runs out)."""
+    from paper_1207_1571_amd import fvm
+    case = _case(shape, None, kind).with_(precision=wl.MIXED)
+    if numbering == "rcm":
+        case = case.with_(mesh=mg.rcm(mg.random_permutation(case.mesh, 3)))
+    inputs = _inputs(case.mesh, 6)
+    c = fvm.Case(case)
+    hook = _hook()
+    for tol, max_iter in ((1e-6, 10000), (1e-9, 37)):
+        hook(20000, 1)
+        try:
+            st_l, info_l, p_l = _solve(c, inputs, tol, max_iter)
+        finally:
+            hook(0, 0)
+        st, info, p = _solve(c, inputs, tol, max_iter)
+        print(f"[resident mixed] {shape} {numbering} iters {info['iters']}", file=sys.stderr, flush=True)
+        assert st == st_l and info == info_l
+        assert np.array_equal(p, p_l)
+
+
+def test_mixed_cases_sharing_launches():
+    from paper_1207_1571_amd import fvm
+    specs = [_case((40, 40, 30)), _case((64, 64, 40), None, "duct"), _case((90, 80, 70)), _case((72, 72, 70), None, "duct"),
+             _case((50, 40, 30), 4), _case((220, 200, 1))]
+    specs = [s.with_(precision=wl.MIXED, p_ctl=wl.SolverCtl(1e-5, max_iter=60), u_ctl=wl.SolverCtl(1e-6)) for s in specs]
+    alone = []
+    for s in specs:
+        c = fvm.Case(s)
+        c.piso(1)
+        alone.append(c.get_state_numpy())
+        c.close()
+    cases = [fvm.Case(s) for s in specs]
+    fvm.piso_batch(cases, 1)
+    for c, a in zip(cases, alone):
+        for x, y in zip(c.get_state_numpy(), a):
+            assert np.array_equal(x, y)
