@@ -176,7 +176,7 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
     d.face_user = b.take<int32_t>(Fi); d.face_sign = b.take<int32_t>(Fi);
     d.patch_uk = b.take<int32_t>(np); d.patch_pk = b.take<int32_t>(np);
     d.patch_uv = b.take<double>(3 * np); d.patch_pv = b.take<double>(np);
-    d.Sx = b.take<double>(F); d.Sy = b.take<double>(F); d.Sz = b.take<double>(F); d.V = b.take<double>(N);
+    d.fg = b.take<double>(4 * F); d.V = b.take<double>(N);
     d.w = b.take<double>(Fi); d.dl = b.take<double>(F);
     if (no) { d.kx = b.take<double>(Fi); d.ky = b.take<double>(Fi); d.kz = b.take<double>(Fi); }
     d.U = b.take<double>(3 * N); d.p = b.take<double>(N); d.phi = b.take<double>(F); d.p_prev = b.take<double>(N);
@@ -544,9 +544,11 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     UPCHK(up(d.bnd_start, m->bnd_start, s)); UPCHK(up(d.bnd_list, m->bnd_list, s)); UPCHK(up(d.bpatch, m->bpatch, s));
     UPCHK(up(d.face_user, m->face_user, s)); UPCHK(up(d.face_sign, m->face_sign, s));
     UPCHK(up(d.patch_uk, uk, s)); UPCHK(up(d.patch_pk, pk, s)); UPCHK(up(d.patch_uv, uv, s)); UPCHK(up(d.patch_pv, pv, s));
-    UPCHK(hipMemcpyAsync(d.Sx, m->S.data(), sizeof(double) * F, hipMemcpyHostToDevice, s));
-    UPCHK(hipMemcpyAsync(d.Sy, m->S.data() + F, sizeof(double) * F, hipMemcpyHostToDevice, s));
-    UPCHK(hipMemcpyAsync(d.Sz, m->S.data() + 2 * F, sizeof(double) * F, hipMemcpyHostToDevice, s));
+    // face area vectors: into face arrays that are free until the first step;
+    // launch_geometry forms the face records from them
+    UPCHK(hipMemcpyAsync(d.phiH, m->S.data(), sizeof(double) * F, hipMemcpyHostToDevice, s));
+    UPCHK(hipMemcpyAsync(d.gam, m->S.data() + F, sizeof(double) * F, hipMemcpyHostToDevice, s));
+    UPCHK(hipMemcpyAsync(d.phi_save, m->S.data() + 2 * F, sizeof(double) * F, hipMemcpyHostToDevice, s));
     UPCHK(up(d.V, m->V, s));
     UPCHK(up(d.tmpC, m->C, s));
     UPCHK(up(d.tmpCf, m->Cf, s));
@@ -1352,8 +1354,7 @@ extern "C" fvm_status solve_pressure(fvm_case *c, const double *gamma, const dou
     const DevCase &d = c->d;
     // the case's p field is the solver's unknown: park it
     HIPCHK(hipMemcpyAsync(d.p_save, d.p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
-    launch_gather_faces(g.bs, gamma, d.phiH, s);
-    launch_p_system_from_gamma(g.bs, d.phiH, rhs, s);
+    launch_p_system_from_gamma(g.bs, gamma, rhs, s);
     HIPCHK(hipMemcpyAsync(d.p, p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     std::vector<KState> res;
     fvm_status st = run_solve(g, 1, 2, ctl, res);
@@ -1437,8 +1438,7 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     batch_add(bs, h.self, &h);
     launch_clear_reduction(bs, s);
     HIPCHK(hipMemcpyAsync(d.p_save, d.p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
-    launch_gather_faces(bs, gamma, d.phiH, s);
-    launch_p_system_from_gamma(bs, d.phiH, rhs, s);
+    launch_p_system_from_gamma(bs, gamma, rhs, s);
     HIPCHK(hipMemcpyAsync(d.p, p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     KState ks{};
     bool launched = true;
@@ -1489,8 +1489,7 @@ extern "C" fvm_status fvm_dic_apply(fvm_case *c, const double *gamma, const doub
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Group g(c, s);
     const DevCase &d = c->d;
-    launch_gather_faces(g.bs, gamma, d.phiH, s);
-    launch_p_system_from_gamma(g.bs, d.phiH, r, s);
+    launch_p_system_from_gamma(g.bs, gamma, r, s);
     HIPCHK(hipMemcpyAsync(d.r, r, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     launch_dic_reset(g.bs, s);
     launch_dic_precond(g.bs, 1, s);

@@ -235,7 +235,8 @@ struct DevCase {
     int32_t *patch_uk, *patch_pk;
     double *patch_uv, *patch_pv;    // [npatch*3], [npatch]
     // geometry (SoA)
-    double *Sx, *Sy, *Sz, *V;
+    double *fg;      // [F][4]: face area vector and weight (1 on boundary faces)
+    double *V;
     double *w, *dl, *kx, *ky, *kz;  // w, k: internal faces; dl: all faces
     // fields
     double *U;       // [3][N]
@@ -350,8 +351,7 @@ void launch_U_in(const BatchSet &bs, const double *U_user, hipStream_t s);
 void launch_U_out(const BatchSet &bs, double *U_user, hipStream_t s);
 void launch_phi_in(const BatchSet &bs, const double *phi_user, hipStream_t s);
 void launch_phi_out(const BatchSet &bs, double *phi_user, hipStream_t s);
-void launch_gather_faces(const BatchSet &bs, const double *user_face_vals, double *canon, hipStream_t s);
-void launch_p_system_from_gamma(const BatchSet &bs, const double *gamma_canon, const double *rhs, hipStream_t s);
+void launch_p_system_from_gamma(const BatchSet &bs, const double *gamma, const double *rhs, hipStream_t s);
 void launch_init_partials(const BatchSet &bs, hipStream_t s);
 void launch_clear_reduction(const BatchSet &bs, hipStream_t s);   // partials at the sentinel, tickets at 0
 // static scratch of solve_pressure_static (kernels.hip): the current
