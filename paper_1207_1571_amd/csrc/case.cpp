@@ -281,7 +281,7 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
         d.hy_w = b.take<double>(E); d.hy_dl = b.take<double>(E); d.hy_g = b.take<double>(E); d.hy_phi = b.take<double>(E);
     }
     {
-        const PartsHost &P = mixed ? mesh_tile_parts(m) : mesh_parts(m);
+        const PartsHost &P = mixed ? mesh_tile_parts(m) : dic ? mesh_level_parts(m) : mesh_parts(m);
         d.res_G = P.G; d.res_W = P.W; d.res_n = P.n_max; d.res_local = P.local_max; d.res_halo_max = P.halo_max;
         if (P.G > 0) {
             d.res_start = b.take<int32_t>(P.start.size()); d.res_hstart = b.take<int32_t>(P.hstart.size());
@@ -579,7 +579,9 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     UPCHK(up(d.sell_off, m->sell_off, s)); UPCHK(up(d.sell_mir, m->sell_mir, s));
     UPCHK(up(d.sell_fe, m->sell_fe, s)); UPCHK(up(d.sell_col, m->sell_col, s));
     if (d.res_G > 0) {
-        const PartsHost &P = o->precision == FVM_MIXED ? mesh_tile_parts(*m) : mesh_parts(*m);
+        const PartsHost &P = o->precision == FVM_MIXED            ? mesh_tile_parts(*m)
+                             : o->p_ctl.precond == FVM_PC_DIC ? mesh_level_parts(*m)
+                                                              : mesh_parts(*m);
         UPCHK(up(d.res_start, P.start, s)); UPCHK(up(d.res_hstart, P.hstart, s)); UPCHK(up(d.res_cell, P.cell, s));
         UPCHK(up(d.res_fe, P.fe, s)); UPCHK(up(d.res_idx, P.idx, s)); UPCHK(up(d.res_halo, P.halo, s));
         UPCHK(up(d.res_far, P.far, s)); UPCHK(up(d.res_shown, P.shown, s)); UPCHK(up(d.res_pub, P.pub, s));
@@ -942,7 +944,8 @@ fvm_status resident_launch(ResidentBatch &rb, const fvm_solver_ctl *ctl, int ser
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
-    if (rb.bs.host[0]->f_x) launch_res_rr(rb.bs, rb.cs, rb.pt, t_res_ticks, serial, s);
+    if (rb.bs.host[0]->dstar) launch_res_dic(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
+    else if (rb.bs.host[0]->f_x) launch_res_rr(rb.bs, rb.cs, rb.pt, t_res_ticks, serial, s);
     else launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
     HIPCHK(hipGetLastError());
     HIPCHK(hipEventRecord(R->last, s));
@@ -978,16 +981,21 @@ fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solv
 // One solve for every case of the group.  kind 0: momentum BiCG (systems
 // 0..2), kind 1: pressure CG (system 3).  ctl_src selects the controls:
 // 0/1 = the cases' own momentum / pressure controls, 2 = *ctl.
-// FVM_MIXED cases run the mixed-precision variants.  Jacobi pressure solves
-// run resident where the case has parts for it; a case's choice does not
+// FVM_MIXED cases run the mixed-precision variants.  Jacobi and DIC pressure
+// solves run resident where the case has parts for it; a case's choice does not
 // depend on the others of the group.
 fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res)
 {
     const int precond = ctl_src == 2 ? ctl->precond : g.cs[0]->o.p_ctl.precond;
     std::vector<int> on;
-    if (kind == 1 && precond == FVM_PC_JACOBI && resident_usable())
+    // a DIC case's parts are in level order, for DIC solves; the others' serve
+    // Jacobi solves
+    auto fits = [&](const fvm_case *c) {
+        return c->d.res_G > 0 && precond == (c->d.dstar ? FVM_PC_DIC : FVM_PC_JACOBI);
+    };
+    if (kind == 1 && precond != FVM_PC_AMG && resident_usable())
         for (int i = 0; i < g.n(); ++i)
-            if (g.cs[i]->d.res_G > 0) on.push_back(i);
+            if (fits(g.cs[i])) on.push_back(i);
     if (on.empty()) return run_launched(g, kind, ctl_src, ctl, res);
     const int serial = resident_serial();
     if (g.cs[0]->o.precision == FVM_MIXED) {
@@ -1004,7 +1012,7 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
         if (!g.rest) {
             std::vector<fvm_case *> off;
             for (auto *c : g.cs)
-                if (c->d.res_G == 0) off.push_back(c);
+                if (!fits(c)) off.push_back(c);
             g.rest = std::make_shared<Group>(off.data(), (int)off.size(), g.poll, g.s);
         }
         st = run_launched(*g.rest, kind, ctl_src, ctl, res);
@@ -1442,7 +1450,7 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     HIPCHK(hipMemcpyAsync(d.p, p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     KState ks{};
     bool launched = true;
-    if (d.res_G > 0 && resident_usable()) {
+    if (d.res_G > 0 && !d.dstar && resident_usable()) {
         ResidentBatch rb;
         rb.add(h.self, h);
         launch_res_reset(bs, 0, s);

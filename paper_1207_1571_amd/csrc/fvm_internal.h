@@ -25,12 +25,18 @@ constexpr int kAmgTailLds = 64 * 1024;   // LDS bytes of the fused smallest-leve
 // than 6 neighbours per cell, halos larger than the LDS)
 struct PartsHost;
 const PartsHost &mesh_parts(const fvm_mesh &m);
+const PartsHost &mesh_level_parts(const fvm_mesh &m);  // the same parts, cells in level order (resident_dic.h)
 const PartsHost &mesh_tile_parts(const fvm_mesh &m);   // parts in the cells' order (resident_rr.h)
 constexpr int kResCells = 4096;       // largest part (512 threads of 8 cells)
 constexpr int kResParts = 256;        // most parts of a case: one workgroup per CU
 constexpr int kResGroup = 32;         // parts of a group: the CUs of an XCD
 constexpr int kResGroups = kResParts / kResGroup;
 constexpr int kResLocal = 7680;       // own cells and halo of a part: 12 bytes of LDS for each, 16 per own cell
+constexpr int kDicLds = 158 * 1024;   // level parts: p and a sweep's values of own cells and halo, x, the halo's positions
+constexpr uint32_t kDicShown = 1u << 30, kDicFar = 1u << 29;   // level parts, beside a cell's index: another part, a part
+                                      // of another group reads it
+constexpr uint32_t kDicLow = 1u << 30, kDicHigh = 1u << 29, kDicPos = kDicHigh - 1;   // and beside a halo cell's position:
+                                      // a lower / an upper entry of a cell of the part
 constexpr int kResGens = 4;           // generations of reduction slots
 constexpr int kResMaxSum = 4;         // sums per reduction (slots laid out)
 #ifdef __HIPCC__
@@ -169,7 +175,7 @@ struct fvm_mesh {
     // slots mirrored from the upper ones, every neighbour inside the mesh
     int32_t sell_n7 = 0;
     mutable std::shared_ptr<AmgHost> amg;   // AMG hierarchy, built on first use
-    mutable std::shared_ptr<PartsHost> parts, tile_parts;   // parts of the resident CG, built on first use
+    mutable std::shared_ptr<PartsHost> parts, tile_parts, level_parts;   // parts of the resident CG, built on first use
 };
 
 // ---------------------------------------------------------------------------
@@ -420,6 +426,9 @@ void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, con
                    int serial, hipStream_t s);
 void launch_res_reset(const BatchSet &bs, int serial, hipStream_t s);
 int res_prepare();
+// the DIC solve (cases laid out with level parts)
+void launch_res_dic(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,
+                    int serial, hipStream_t s);
 // the mixed-precision solve: start (residual, FP32 copies, first rho) and the
 // resident recurrence
 void launch_rr_resident_start(const BatchSet &bs, hipStream_t s);

@@ -33,6 +33,8 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "fvm_internal.h"
 
@@ -2684,6 +2686,7 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
 
 #include "resident_cg.h"
 #include "resident_rr.h"
+#include "resident_dic.h"
 
 // ---------------------------------------------------------------------------
 // Whole PISO steps of small cases, one workgroup per case
@@ -4488,10 +4491,14 @@ int res_prepare()
                 return 1;
             }
         }
-    for (const void *k : {(const void *)k_res_rr<4>, (const void *)k_res_rr<6>}) {
+    const std::pair<const void *, int> others[] = {{(const void *)k_res_rr<4>, kRrLds},
+                                                   {(const void *)k_res_rr<6>, kRrLds},
+                                                   {(const void *)k_res_dic<4>, kDicLds},
+                                                   {(const void *)k_res_dic<6>, kDicLds}};
+    for (const auto &k : others) {
         int blocks = 0;
-        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kRrLds) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, kResThreads, kRrLds) != hipSuccess || blocks < 1) {
+        if (hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, k.second) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k.first, kResThreads, k.second) != hipSuccess || blocks < 1) {
             (void)hipGetLastError();
             return 1;
         }
@@ -4521,6 +4528,27 @@ void launch_res_rr(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, lon
         lds = std::max(lds, sizeof(float) * (size_t)bs.host[c]->res_local + sizeof(int32_t) * (size_t)bs.host[c]->res_halo_max);
     hipLaunchKernelGGL(bs.host[0]->res_W == 4 ? k_res_rr<4> : k_res_rr<6>, dim3((unsigned)grid), dim3(kResThreads), lds, s,
                        bs.b[SZ_CELL], map, serial, ticks);
+}
+
+void launch_res_dic(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,
+                    int serial, hipStream_t s)
+{
+    Prof p("pcg_dic_resident", s);
+    ResMap map;
+    int grid = 0;
+    size_t lds = 0;
+    for (int b = 0; b < kResParts; ++b) {
+        map.cs[b] = cs[b];
+        map.pt[b] = pt[b];
+        if (cs[b] != 255) grid = b + 1;
+    }
+    // the vector's length is the case's own: the largest decides the launch's LDS
+    for (int c = 0; c < bs.n; ++c)
+        lds = std::max(lds, sizeof(double) * (2 * (size_t)bs.host[c]->res_local + 1 + kResCells + 2 * kResCells / 64) +
+                                sizeof(int32_t) * (size_t)bs.host[c]->res_halo_max);
+    const ResCtl rc{ctl ? ctl->tol : 0.0, ctl ? ctl->rel_tol : 0.0, ctl ? ctl->max_iter : 0, ctl ? 1 : 0, serial};
+    hipLaunchKernelGGL(bs.host[0]->res_W == 4 ? k_res_dic<4> : k_res_dic<6>, dim3((unsigned)grid), dim3(kDicThreads), lds, s,
+                       bs.b[SZ_CELL], map, rc, ticks);
 }
 
 void launch_res_cg(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,

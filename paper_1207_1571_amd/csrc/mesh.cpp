@@ -519,11 +519,14 @@ namespace {
 
 struct PartCell {
     double c[3];
-    int32_t i;
+    int32_t i, lvl;   // cell; its dependency level (0 where the order inside a plane is the cells')
 };
 
 // the cells [a, a + n) into g parts of nearly equal size: split across the
-// longest extent of their centres, in proportion, until g == 1
+// longest extent of their centres, in proportion, until g == 1.  A plane of
+// cells that falls on the split is divided by level, its cells of low levels
+// going to the side of low levels: a chain of dependent cells then crosses
+// the split once, not to and fro.
 void bisect(PartCell *a, int32_t n, int32_t g, std::vector<int32_t> &size)
 {
     if (g == 1) {
@@ -541,8 +544,14 @@ void bisect(PartCell *a, int32_t n, int32_t g, std::vector<int32_t> &size)
     for (int k = 1; k < 3; ++k)
         if (hi[k] - lo[k] > hi[ax] - lo[ax]) ax = k;
     const int32_t gl = g / 2, nl = (int32_t)((int64_t)n * gl / g);
-    std::nth_element(a, a + nl, a + n, [ax](const PartCell &x, const PartCell &y) {
-        return x.c[ax] != y.c[ax] ? x.c[ax] < y.c[ax] : x.i < y.i;
+    const double mid = 0.5 * (lo[ax] + hi[ax]);
+    double low = 0.0, high = 0.0, nlow = 0.0;
+    for (int32_t j = 0; j < n; ++j)
+        if (a[j].c[ax] < mid) { low += a[j].lvl; nlow += 1.0; }
+        else high += a[j].lvl;
+    const bool falls = low * (n - nlow) > high * nlow;
+    std::nth_element(a, a + nl, a + n, [ax, falls](const PartCell &x, const PartCell &y) {
+        return x.c[ax] != y.c[ax] ? x.c[ax] < y.c[ax] : x.lvl != y.lvl ? (x.lvl < y.lvl) != falls : x.i < y.i;
     });
     bisect(a, nl, gl, size);
     bisect(a + nl, n - nl, g - gl, size);
@@ -551,7 +560,7 @@ void bisect(PartCell *a, int32_t n, int32_t g, std::vector<int32_t> &size)
 // entries, local places and halos of the parts of h (start, cell set); false
 // when a part's own cells and halo exceed `limit`
 bool fill_parts(const fvm_mesh &m, PartsHost &h, const std::vector<int32_t> &part, const std::vector<int32_t> &pos,
-                int32_t W, int32_t limit)
+                int32_t W, int32_t limit, bool by_level = false)
 {
     const int32_t N = m.N, G = (int32_t)h.start.size() - 1;
     std::vector<int32_t> mark(N, -1), where(N), found;
@@ -571,7 +580,10 @@ bool fill_parts(const fvm_mesh &m, PartsHost &h, const std::vector<int32_t> &par
             for (int32_t k = m.nbr_start[i]; k < m.nbr_start[i + 1]; ++k) others(m.own[m.losort[k]]);
             for (int32_t f = m.own_start[i]; f < m.own_start[i + 1]; ++f) others(m.nei[f]);
         }
-        std::sort(found.begin(), found.end());
+        std::sort(found.begin(), found.end(), [&](int32_t a, int32_t b) {
+            const int32_t la = by_level ? m.lvl_of[h.cell[a]] : 0, lb = by_level ? m.lvl_of[h.cell[b]] : 0;
+            return la != lb ? la < lb : a < b;
+        });
         const int32_t H = (int32_t)found.size();
         if (n + H > limit) return false;
         h.halo_max = std::max(h.halo_max, H);
@@ -614,7 +626,7 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
     }
     const int32_t W = m.sell_W <= 4 ? 4 : 6;
     std::vector<PartCell> a(N);
-    for (int32_t i = 0; i < N; ++i) a[i] = PartCell{{m.C[i], m.C[(size_t)N + i], m.C[2 * (size_t)N + i]}, i};
+    for (int32_t i = 0; i < N; ++i) a[i] = PartCell{{m.C[i], m.C[(size_t)N + i], m.C[2 * (size_t)N + i]}, i, 0};
     std::vector<int32_t> size;
     bisect(a.data(), N, G, size);
     std::vector<int32_t> pos(N), part(N);
@@ -661,6 +673,59 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
     return *h;
 }
 
+
+const PartsHost &mesh_level_parts(const fvm_mesh &m)
+{
+    if (m.level_parts) return *m.level_parts;
+    auto h = std::make_shared<PartsHost>();
+    const int32_t N = m.N, G = (N + kResCells - 1) / kResCells, W = m.sell_W <= 4 ? 4 : 6;
+    if (G <= kResParts && m.sell_W <= 6) {
+        std::vector<PartCell> a(N);
+        for (int32_t i = 0; i < N; ++i)
+            a[i] = PartCell{{m.C[i], m.C[(size_t)N + i], m.C[2 * (size_t)N + i]}, i, m.lvl_of[i]};
+        std::vector<int32_t> size, part(N), pos(N);
+        bisect(a.data(), N, G, size);
+        h->start.assign(1, 0);
+        h->cell.resize(N);
+        h->far.assign(G, 0);
+        h->shown.assign(G, 0);
+        h->hstart.assign(1, 0);
+        for (int32_t p = 0, at = 0; p < G; at += size[p++]) {
+            std::sort(a.begin() + at, a.begin() + at + size[p], [](const PartCell &x, const PartCell &y) {
+                return x.lvl != y.lvl ? x.lvl < y.lvl : x.i < y.i;
+            });
+            for (int32_t q = at; q < at + size[p]; ++q) {
+                h->cell[q] = a[q].i;
+                part[a[q].i] = p;
+                pos[a[q].i] = q;
+            }
+            h->start.push_back(at + size[p]);
+        }
+        if (fill_parts(m, *h, part, pos, W, 65535, true) &&
+            2 * 8 * (int64_t)h->local_max + 8 * (kResCells + 1 + 2 * kResCells / 64) + 4 * (int64_t)h->halo_max <= kDicLds) {
+            for (int32_t p = 0; p < G; ++p) {
+                const int32_t n = h->start[p + 1] - h->start[p];
+                const size_t base = (size_t)W * h->start[p];
+                for (size_t e = base; e < base + (size_t)W * n; ++e)
+                    if (h->fe[e] >= 0 && h->idx[e] >= n) {
+                        int32_t &q = h->halo[h->hstart[p] + h->idx[e] - n];
+                        q = (int32_t)((uint32_t)q | (h->fe[e] & 1 ? kDicLow : kDicHigh));
+                    }
+            }
+            std::vector<uint32_t> flag(N, 0);
+            for (int32_t f = 0; f < m.Fi; ++f) {
+                const int32_t a = m.own[f], b = m.nei[f];
+                if (part[a] == part[b]) continue;
+                const uint32_t v = kDicShown | (res_group_of(part[a], G) != res_group_of(part[b], G) ? kDicFar : 0u);
+                flag[a] |= v;
+                flag[b] |= v;
+            }
+            for (int32_t q = 0; q < N; ++q) h->cell[q] = (int32_t)((uint32_t)h->cell[q] | flag[h->cell[q]]);
+        } else *h = PartsHost();
+    }
+    m.level_parts = h;
+    return *h;
+}
 
 const PartsHost &mesh_tile_parts(const fvm_mesh &m)
 {

@@ -157,7 +157,7 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, par = tm.gen & 1;
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] = wave_total(v[k]);
-    if (lane == 0)
+    if (lane == 0 && wv < kResWaves)   // further waves have no cells
 #pragma unroll
         for (int k = 0; k < NV; ++k) sh.part[par][k][wv] = v[k];
     wait_vmem();
@@ -453,17 +453,11 @@ struct ResMap {
     uint8_t cs[kResParts], pt[kResParts];
 };
 
-template <int W, int U>
-__global__ void __launch_bounds__(kResThreads) k_res_cg(Batch bt, ResMap map, ResCtl ctl, long ticks)
+__device__ __forceinline__ ResTeam res_team(const DevCase &d, int part, long ticks)
 {
-    extern __shared__ __align__(16) double res_lds[];
-    __shared__ ResRed sh;
-    const int c = map.cs[blockIdx.x];
-    if (c >= bt.n) return;
-    const DevCase &d = *bt.dc[c];
     ResTeam tm;
     tm.slots = d.res_slots;
-    tm.part = map.pt[blockIdx.x];
+    tm.part = part;
     tm.G = d.res_G;
     tm.gen = *d.res_gen;
     tm.ngrp = res_groups(tm.G);
@@ -472,13 +466,29 @@ __global__ void __launch_bounds__(kResThreads) k_res_cg(Batch bt, ResMap map, Re
     tm.size = res_group_first(tm.grp + 1, tm.G) - tm.first;
     tm.local = false;
     tm.ticks = ticks;
+    return tm;
+}
+
+// the next solve goes on with the generation after this one's last (its
+// slots are emptied then)
+__device__ __forceinline__ void res_end(const DevCase &d, const ResTeam &tm, bool ok)
+{
+    if (threadIdx.x != 0) return;
+    if (!ok) d.ks[kNumKs - 1].pad[0] = 1;
+    else if (tm.part == 0) *d.res_gen = tm.gen & (kResGens - 1);
+}
+
+template <int W, int U>
+__global__ void __launch_bounds__(kResThreads) k_res_cg(Batch bt, ResMap map, ResCtl ctl, long ticks)
+{
+    extern __shared__ __align__(16) double res_lds[];
+    __shared__ ResRed sh;
+    const int c = map.cs[blockIdx.x];
+    if (c >= bt.n) return;
+    const DevCase &d = *bt.dc[c];
+    ResTeam tm = res_team(d, map.pt[blockIdx.x], ticks);
     const bool ok = res_solve<W, U>(d, tm, ctl, sh, res_lds);
-    // the next solve goes on with the generation after this one's last (its
-    // slots are emptied then)
-    if (threadIdx.x == 0) {
-        if (!ok) d.ks[kNumKs - 1].pad[0] = 1;
-        else if (tm.part == 0) *d.res_gen = tm.gen & (kResGens - 1);
-    }
+    res_end(d, tm, ok);
 }
 
 // slots empty, generation 0, no wait run out (ks[kNumKs - 1].pad[0]; case
@@ -499,5 +509,8 @@ __global__ void k_res_reset(Batch bt, int serial)
     for (int part = K.raw; serial > 0 && part < d.res_G; part += K.G)
         if (d.res_fin[part] == serial)
             for (int q = d.res_start[part] + threadIdx.x; q < d.res_start[part + 1]; q += kBlock)
-                d.p[d.res_cell[q]] = d.rt[d.res_cell[q]];
+            {
+                const int i = (int)((unsigned int)d.res_cell[q] & ~(kDicShown | kDicFar));
+                d.p[i] = d.rt[i];
+            }
 }

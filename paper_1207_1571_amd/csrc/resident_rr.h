@@ -387,8 +387,5 @@ __global__ void __launch_bounds__(kResThreads) k_res_rr(Batch bt, ResMap map, in
     tm.local = false;
     tm.ticks = ticks;
     const bool ok = rr_solve<W>(d, tm, serial, sh, rr_lds);
-    if (threadIdx.x == 0) {
-        if (!ok) d.ks[kNumKs - 1].pad[0] = 1;
-        else if (tm.part == 0) *d.res_gen = tm.gen & (kResGens - 1);
-    }
+    res_end(d, tm, ok);
 }

@@ -215,3 +215,60 @@ def test_mixed_cases_sharing_launches():
     for c, a in zip(cases, alone):
         for x, y in zip(c.get_state_numpy(), a):
             assert np.array_equal(x, y)
+
+
+# DIC: one part; two; jagged parts of one group; three groups; sheet; cells
+# with up to 6 lower neighbours (random numbering); a duct in its own order
+@pytest.mark.parametrize("shape,numbering,kind", [
+    ((16, 16, 16), "lex", "cavity"), ((17, 16, 16), "rcm", "cavity"), ((33, 31, 30), "rcm", "cavity"),
+    ((66, 64, 63), "rcm", "cavity"), ((230, 90, 1), "random", "cavity"), ((40, 36, 30), "random", "cavity"),
+    ((80, 30, 30), "lex", "duct")])
+def test_dic_against_oracle(shape, numbering, kind):
+    """And after a launch whose wait ran out, which leaves the solve to the
+    launched sweeps.  25 iterations each: past some 100 iterations on a sheet
+    the recurrence amplifies rounding (two runs of the launched sweeps then
+    differ from each other by 3e-7)."""
+    import torch
+    from paper_1207_1571_amd import fvm
+    case = _case(shape, None, kind).with_(p_ctl=wl.SolverCtl(1e-9, precond=wl.PC_DIC))
+    if numbering != "lex":
+        mesh = mg.random_permutation(case.mesh, 3)
+        case = case.with_(mesh=mg.rcm(mesh) if numbering == "rcm" else mesh)
+    inputs = _inputs(case.mesh, 7)
+    c, oc, hook = fvm.Case(case), orc.OracleCase(case), _hook()
+    for tol, max_iter, out in ((1e-12, 25, 0), (1e-12, 25, 1), (1e-12, 25, 0)):
+        g, r, p = (torch.from_numpy(a.copy()).cuda() for a in inputs)
+        torch.cuda.synchronize()
+        if out and case.mesh.n_cells > 4096:   # of one part there is nothing to leave out
+            hook(20000, 1)
+        try:
+            st, info = c.solve_pressure(g, r, p, tol, max_iter=max_iter, precond=wl.PC_DIC)
+        finally:
+            hook(0, 0)
+        torch.cuda.synchronize()
+        po = inputs[2].copy()
+        st_o, info_o = oc.solve_pressure(inputs[0], inputs[1], po, tol, max_iter=max_iter, precond=wl.PC_DIC)
+        err = np.linalg.norm(p.cpu().numpy() - po) / np.linalg.norm(po)
+        print(f"[resident DIC] {shape} {numbering} iters {info['iters']}/{info_o['iters']} rel {err:.1e}", file=sys.stderr, flush=True)
+        assert st == st_o and info["iters"] == info_o["iters"]
+        assert err <= TOL
+
+
+def test_dic_cases_sharing_launches():
+    """Also with cases too large for the resident sweeps' parts next to them."""
+    from paper_1207_1571_amd import fvm
+    specs = [_case((12, 10, 9), 1), _case((70, 70, 1), 2), _case((64, 64, 40)), _case((90, 80, 70)),
+             _case((96, 80, 70), None, "duct"), _case((104, 104, 104))]
+    specs = [s.with_(step_kernel=wl.STEP_LAUNCHED, p_ctl=wl.SolverCtl(1e-5, max_iter=20, precond=wl.PC_DIC),
+                     u_ctl=wl.SolverCtl(1e-6)) for s in specs]
+    alone = []
+    for s in specs:
+        c = fvm.Case(s)
+        c.piso(1)
+        alone.append(c.get_state_numpy())
+        c.close()
+    cases = [fvm.Case(s) for s in specs]
+    fvm.piso_batch(cases, 1)
+    for k, (c, a) in enumerate(zip(cases, alone)):
+        for x, y in zip(c.get_state_numpy(), a):
+            assert np.linalg.norm(x - y) <= TOL * np.linalg.norm(y), k
