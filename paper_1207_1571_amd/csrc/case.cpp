@@ -301,7 +301,7 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
     d.red_stride2 = (d.red_stride + kGroup - 1) / kGroup;
     d.partials = b.take<double>((size_t)kMaxRed * d.red_stride);
     d.partials2 = b.take<double>((size_t)kMaxRed * d.red_stride2);
-    d.gticket = b.take<unsigned int>((size_t)d.red_stride2);
+    d.gticket = b.take<unsigned int>((size_t)d.red_stride2 * kTicketStep);
     d.ticket = b.take<unsigned int>(64);
     d.ks = b.take<KState>(kNumKs);
     d.ks_gather = b.take<KState>((size_t)kMaxBatch * kNumKs);
@@ -619,7 +619,7 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
             UPCHK(hipMemsetAsync(a, 0, E * sizeof(double), s));
     }
     UPCHK(hipMemsetAsync(d.ticket, 0, 64 * sizeof(unsigned int), s));
-    UPCHK(hipMemsetAsync(d.gticket, 0, d.red_stride2 * sizeof(unsigned int), s));
+    UPCHK(hipMemsetAsync(d.gticket, 0, (size_t)d.red_stride2 * kTicketStep * sizeof(unsigned int), s));
     UPCHK(hipMemsetAsync(d.ks, 0, kNumKs * sizeof(KState), s));
     if (d.res_G > 0) UPCHK(hipMemsetAsync(d.res_fin, 0, sizeof(int32_t) * d.res_G, s));
     const Group g(c, s);
@@ -1390,7 +1390,7 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
     unsigned char *self = take(sizeof(DevCase));
     unsigned char *p1 = take(sizeof(double) * (size_t)kMaxRed * d.red_stride);
     unsigned char *p2 = take(sizeof(double) * (size_t)kMaxRed * d.red_stride2);
-    unsigned char *gt = take(sizeof(unsigned int) * (size_t)d.red_stride2);
+    unsigned char *gt = take(sizeof(unsigned int) * (size_t)d.red_stride2 * kTicketStep);
     unsigned char *tk = take(sizeof(unsigned int) * 64);
     unsigned char *ks = take(sizeof(KState) * kNumKs);
     unsigned char *rs = d.res_G > 0 ? take(sizeof(double) * (size_t)std::max(1, d.res_words)) : nullptr;

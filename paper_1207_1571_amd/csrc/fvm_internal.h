@@ -211,6 +211,7 @@ constexpr int32_t kStatusFallback = 3;
 
 constexpr int kBlock = 256;
 constexpr int kGroup = 64;           // blocks per first-level reduction group
+constexpr int kTicketStep = 32;      // words between two groups' tickets: a cache line each
 constexpr int kMaxRed = 12;          // reduced quantities per kernel
 constexpr int kNumKs = 8;            // Krylov states per case
 
@@ -311,7 +312,7 @@ struct DevCase {
     double *partials;                            // [kMaxRed][red_stride]   level-1 slots
     double *partials2;                           // [kMaxRed][red_stride2]  level-2 slots
     int32_t red_stride, red_stride2;             // >= any reducing grid, and its groups
-    unsigned int *gticket;                       // [red_stride2] group tickets
+    unsigned int *gticket;                       // [red_stride2 * kTicketStep] group tickets
     unsigned int *ticket;
     KState *ks;                                  // [8]: 0..2 momentum, 3 pressure; 4..7 their FP32 inner solves
     // setup temporaries (alias Krylov vectors)

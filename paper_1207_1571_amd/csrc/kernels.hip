@@ -34,7 +34,6 @@
 #include <cmath>
 #include <mutex>
 #include <type_traits>
-#include <utility>
 
 #include "fvm_internal.h"
 
@@ -112,33 +111,45 @@ __device__ __forceinline__ Range block_range(int n, const Blk &K)
 // ---------------------------------------------------------------------------
 // reductions
 // ---------------------------------------------------------------------------
+// x moved within the wave by one data-parallel step (zero moved in)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// wave sum, partners 32, 16, 8, 4, 2, 1 apart, by
+// lane swaps and row rotations instead of shuffles through the LDS unit.
+// After the steps 32, 16 and 8 a lane's value depends only on its place in a
+// group of 8, 4, 2 lanes, so a rotation by 4, 2, 1 meets the same partner.
+__device__ __forceinline__ double wave_tree(double x)
+{
+    const unsigned int lo = (unsigned int)__double2loint(x), hi = (unsigned int)__double2hiint(x);
+    {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+    {
+        const unsigned int lo2 = (unsigned int)__double2loint(x), hi2 = (unsigned int)__double2hiint(x);
+        const auto l = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
+        x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+    x += dpp_move<0x128, 0xf>(x);   // row_ror 8, 4, 2, 1
+    x += dpp_move<0x124, 0xf>(x);
+    x += dpp_move<0x122, 0xf>(x);
+    x += dpp_move<0x121, 0xf>(x);
+    return x;
+}
+
 template <int NV>
 __device__ __forceinline__ void wave_sum(double (&v)[NV])
 {
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-}
-
-// fixed-order block sum of NV values; result valid in thread 0
-template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double (&lds)[NV][kWaves])
-{
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    wave_sum(v);
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) lds[k][wv] = v[k];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            double s = lds[k][0];
-            for (int w = 1; w < kWaves; ++w) s += lds[k][w];
-            v[k] = s;
-        }
+    for (int k = 0; k < NV; ++k) v[k] = wave_tree(v[k]);
 }
 
 // Global-address-space view of a device pointer.  Accesses through it are
@@ -198,55 +209,74 @@ __device__ __forceinline__ void slot_put(double *slot, double v)
 // takes its group's ticket (groups of kGroup consecutive tiles); the block
 // that completes a group sums the group's slots in order and publishes one
 // level-2 partial.  Level 2: the block that completes the last group sums
-// the level-2 slots in order.  Returns true in every thread of that final
-// block, with the totals in tot[].
+// the level-2 slots in order.  Returns true in the first wave of that final
+// block, with the totals in tot[]; called once, at the end of a kernel.
+//
+// What bounded the kernels that end in it, below some million cells, were
+// the tickets: the atomics of all groups went to one cache line, one after
+// the other (about 10 ns each, 10 of the 24 us of a product of 1M cells), and
+// every wave of a block waited for the block's.  Groups now have a line each,
+// and only the first wave stays.  The multigrid solve of 1M cells 27.5 ->
+// 23.9 ms by the lines alone, a step of 8M cells 688 -> 680.
 template <int NV>
-__device__ bool reduce_last(double (&v)[NV], const DevCase &d, const Blk &K, double *tot)
+__device__ __forceinline__ bool reduce_last(double (&v)[NV], const DevCase &d, const Blk &K, double *tot)
 {
     __shared__ double lds[NV][kWaves];
-    __shared__ int stage;
     const int G = K.G, lb = K.lb;
     const int grp = lb / kGroup, ngrp = (G + kGroup - 1) / kGroup;
     const int gsize = min(kGroup, G - grp * kGroup);
-    block_sum(v, lds);
-    if (threadIdx.x == 0) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    wave_sum(v);
+    if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < NV; ++k) slot_put(&d.partials[k * d.red_stride + lb], v[k]);
-        const unsigned int t = __hip_atomic_fetch_add(&d.gticket[grp], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stage = t == (unsigned int)gsize - 1;
-    }
+        for (int k = 0; k < NV; ++k) lds[k][wv] = v[k];
     __syncthreads();
-    if (!stage) return false;
+    if (wv != 0) return false;
+    unsigned int t = 0;
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            double s = lds[k][0];
+            for (int w = 1; w < kWaves; ++w) s += lds[k][w];
+            slot_put(&d.partials[k * d.red_stride + lb], s);
+        }
+        t = __hip_atomic_fetch_add(&d.gticket[grp * kTicketStep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(t) != (unsigned int)gsize - 1) return false;
     double g[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) g[k] = 0.0;
-    if ((int)threadIdx.x < gsize) slots_take<NV>(&d.partials[grp * kGroup + threadIdx.x], d.red_stride, g);
-    block_sum(g, lds);
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(&d.gticket[grp], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    static_assert(kGroup <= 64, "a wave takes a group's slots");
+    if (lane < gsize) slots_take<NV>(&d.partials[grp * kGroup + lane], d.red_stride, g);
+    wave_sum(g);
+    if (lane == 0) {
+        __hip_atomic_store(&d.gticket[grp * kTicketStep], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int k = 0; k < NV; ++k) slot_put(&d.partials2[k * d.red_stride2 + grp], g[k]);
-        const unsigned int t = __hip_atomic_fetch_add(d.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stage = t == (unsigned int)ngrp - 1 ? 2 : 0;
+        t = __hip_atomic_fetch_add(d.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
-    if (stage != 2) return false;
-    double a[NV];
+    if (__builtin_amdgcn_readfirstlane(t) != (unsigned int)ngrp - 1) return false;
+    // the sums of kBlock threads, wave by wave
+    double s[NV];
+    for (int w = 0; w < kWaves; ++w) {
+        double a[NV];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) a[k] = 0.0;
-    for (int j = threadIdx.x; j < ngrp; j += kBlock) {
-        double t[NV];
-        slots_take<NV>(&d.partials2[j], d.red_stride2, t);
+        for (int k = 0; k < NV; ++k) a[k] = 0.0;
+        for (int j = w * 64 + lane; j < ngrp; j += kBlock) {
+            double q[NV];
+            slots_take<NV>(&d.partials2[j], d.red_stride2, q);
 #pragma unroll
-        for (int k = 0; k < NV; ++k) a[k] += t[k];
+            for (int k = 0; k < NV; ++k) a[k] += q[k];
+        }
+        if (w == 0 || w * 64 < ngrp) wave_sum(a);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) s[k] = w == 0 ? a[k] : s[k] + a[k];
     }
-    block_sum(a, lds);
-    if (threadIdx.x == 0) {
+    if (lane == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) tot[k] = a[k];
+        for (int k = 0; k < NV; ++k) tot[k] = s[k];
         __hip_atomic_store(d.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
     return true;
 }
 
@@ -714,7 +744,7 @@ __global__ void k_clear_reduction(Batch bt)
     const long n1 = (long)kMaxRed * d.red_stride, n2 = (long)kMaxRed * d.red_stride2;
     for (long i = t; i < n1; i += stride) clear_word(d.partials, i);
     for (long i = t; i < n2; i += stride) clear_word(d.partials2, i);
-    for (long i = t; i < d.red_stride2; i += stride) d.gticket[i] = 0u;
+    for (long i = t; i < (long)d.red_stride2 * kTicketStep; i += stride) d.gticket[i] = 0u;
     for (long i = t; i < 64; i += stride) d.ticket[i] = 0u;
 }
 
@@ -4491,14 +4521,14 @@ int res_prepare()
                 return 1;
             }
         }
-    const std::pair<const void *, int> others[] = {{(const void *)k_res_rr<4>, kRrLds},
-                                                   {(const void *)k_res_rr<6>, kRrLds},
-                                                   {(const void *)k_res_dic<4>, kDicLds},
-                                                   {(const void *)k_res_dic<6>, kDicLds}};
+    const struct { const void *kernel; int lds, threads; } others[] = {{(const void *)k_res_rr<4>, kRrLds, kResThreads},
+                                                                       {(const void *)k_res_rr<6>, kRrLds, kResThreads},
+                                                                       {(const void *)k_res_dic<4>, kDicLds, kDicThreads},
+                                                                       {(const void *)k_res_dic<6>, kDicLds, kDicThreads}};
     for (const auto &k : others) {
         int blocks = 0;
-        if (hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, k.second) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k.first, kResThreads, k.second) != hipSuccess || blocks < 1) {
+        if (hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k.kernel, k.threads, k.lds) != hipSuccess || blocks < 1) {
             (void)hipGetLastError();
             return 1;
         }

@@ -36,15 +36,6 @@ constexpr int kResThreads = 512;
 constexpr int kResWaves = kResThreads / 64;
 constexpr int kHaloStep = 5;   // halo cells a thread loads at once (a 16^3 brick's halo: 3 to 5 per thread)
 
-// x moved within the wave by one data-parallel step (zero moved in)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_move(double x)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
 // value of one lane, in scalar registers
 __device__ __forceinline__ double lane_value(double x, int lane)
 {

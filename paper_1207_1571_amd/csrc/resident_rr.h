@@ -21,31 +21,6 @@
 
 typedef __attribute__((address_space(1))) unsigned int gword32;
 
-// wave sum in the order of wave_sum (partners 32, 16, 8, 4, 2, 1 apart), by
-// lane swaps and row rotations instead of shuffles through the LDS unit.
-// After the steps 32, 16 and 8 a lane's value depends only on its place in a
-// group of 8, 4, 2 lanes, so a rotation by 4, 2, 1 meets the same partner.
-__device__ __forceinline__ double wave_tree(double x)
-{
-    const unsigned int lo = (unsigned int)__double2loint(x), hi = (unsigned int)__double2hiint(x);
-    {
-        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    }
-    {
-        const unsigned int lo2 = (unsigned int)__double2loint(x), hi2 = (unsigned int)__double2hiint(x);
-        const auto l = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
-        x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    }
-    x += dpp_move<0x128, 0xf>(x);   // row_ror 8, 4, 2, 1
-    x += dpp_move<0x124, 0xf>(x);
-    x += dpp_move<0x122, 0xf>(x);
-    x += dpp_move<0x121, 0xf>(x);
-    return x;
-}
-
 constexpr int kRrTiles = kResCells / kRrTile;     // tiles of a part
 constexpr int kRrU = kResCells / kResThreads;     // cells of a thread
 constexpr int kRrHaloStep = 9;                    // halo cells a thread loads at once
