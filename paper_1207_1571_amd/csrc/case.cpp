@@ -854,6 +854,7 @@ struct ResidentDevice {
     int usable = -1;           // -1: not looked at yet
     hipEvent_t last = nullptr; // recorded after the latest launch
     bool any = false;
+    int solo = 0;              // CUs per XCD that whole-step launches in flight hold
 };
 std::mutex g_res_mu;
 ResidentDevice g_res_dev[64];
@@ -893,13 +894,55 @@ bool resident_usable()
     return resident_device() != nullptr;
 }
 
+// A whole-step launch of n cases on stream s, until it is destroyed (after
+// the launch has ended).  Such a launch holds its CUs for many steps, up to
+// seconds: it starts behind the resident launch in flight, whose workgroups
+// it could otherwise keep off the device, and resident launches keep clear
+// of it meanwhile.  Without that a stream of mixed-precision requests of all
+// sizes took 51 s, its large cases waiting inside their launches for the
+// small ones' steps.
+struct SoloMark {
+    ResidentDevice *R = nullptr;
+    int cus = 0;
+    SoloMark(int n, hipStream_t s) : cus((n + kResGroups - 1) / kResGroups)
+    {
+        std::lock_guard<std::mutex> lk(g_res_mu);
+        R = resident_device();
+        if (!R) return;
+        R->solo += cus;
+        if (R->any) (void)hipStreamWaitEvent(s, R->last, 0);
+    }
+    ~SoloMark()
+    {
+        std::lock_guard<std::mutex> lk(g_res_mu);
+        if (R) R->solo -= cus;
+    }
+    SoloMark(const SoloMark &) = delete;
+    SoloMark &operator=(const SoloMark &) = delete;
+};
+
+// whole-step launches are in flight: mixed solves, whose launched iterations
+// give the same bits, then run as these
+bool solo_in_flight()
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    const ResidentDevice *R = resident_device();
+    return R && R->solo > 0;
+}
+
 // cases that share a launch, and which part each workgroup holds: workgroup
-// 8 k + x runs on XCD x, so a group of parts takes workgroups of one x
+// 8 k + x runs on XCD x, so a group of parts takes workgroups of one x.
+// While whole-step launches hold CUs (room < kResGroup left per XCD), a case
+// whose groups do not fit on the rest, but whose parts do, is spread over
+// the XCDs (the sums are the same, only slower); a larger one takes all CUs
+// and waits for those held.
 struct ResidentBatch {
     BatchSet bs;
     int fill[kResGroups] = {};
     uint8_t cs[kResParts], pt[kResParts];
-    ResidentBatch()
+    int room;
+    bool full = false;
+    explicit ResidentBatch(const ResidentDevice *R) : room(std::max(0, kResGroup - (R ? R->solo : 0)))
     {
         bs.n = 0;
         std::memset(cs, 255, sizeof(cs));
@@ -912,21 +955,37 @@ struct ResidentBatch {
         const bool mixed = d.f_x != nullptr;
         if (bs.n > 0 && bs.host[0]->res_W != d.res_W) return false;
         auto group = [&](int part) { return mixed ? part / kRrGroup : res_group_of(part, G); };
-        int at[kRrGroups], sum[kResGroups];
-        std::copy(fill, fill + kResGroups, sum);
-        for (int part = 0; part < G;) {
-            const int g = group(part);
-            int size = 0;
-            while (part < G && group(part) == g) ++part, ++size;
-            at[g] = -1;
-            // the fullest XCD that still has room
-            for (int x = 0; x < kResGroups; ++x)
-                if (sum[x] + size <= kResGroup && (at[g] < 0 || sum[x] > sum[at[g]])) at[g] = x;
-            if (at[g] < 0) return false;
-            sum[at[g]] += size;
+        if (full) return false;
+        // the XCD of every group: the fullest one that still has room
+        int at[kRrGroups];
+        auto groups_fit = [&](int limit) {
+            int sum[kResGroups];
+            std::copy(fill, fill + kResGroups, sum);
+            for (int part = 0; part < G;) {
+                const int g = group(part);
+                int size = 0;
+                while (part < G && group(part) == g) ++part, ++size;
+                at[g] = -1;
+                for (int x = 0; x < kResGroups; ++x)
+                    if (sum[x] + size <= limit && (at[g] < 0 || sum[x] > sum[at[g]])) at[g] = x;
+                if (at[g] < 0) return false;
+                sum[at[g]] += size;
+            }
+            return true;
+        };
+        bool spread = false;
+        if (!groups_fit(room)) {
+            int left = 0;
+            for (int x = 0; x < kResGroups; ++x) left += room - fill[x];
+            spread = room < kResGroup && left >= G;
+            if (!spread) {
+                if (bs.n > 0 || !groups_fit(kResGroup)) return false;
+                full = room < kResGroup;
+            }
         }
         for (int part = 0; part < G; ++part) {
-            const int x = at[group(part)], b = kResGroups * fill[x]++ + x;
+            const int x = spread ? (int)(std::min_element(fill, fill + kResGroups) - fill) : at[group(part)];
+            const int b = kResGroups * fill[x]++ + x;
             cs[b] = (uint8_t)bs.n;
             pt[b] = (uint8_t)part;
         }
@@ -935,11 +994,9 @@ struct ResidentBatch {
     }
 };
 
-fvm_status resident_launch(ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s)
+// (g_res_mu held)
+fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s)
 {
-    std::lock_guard<std::mutex> lk(g_res_mu);
-    ResidentDevice *R = resident_device();
-    if (!R) return fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
     if (R->any) HIPCHK(hipStreamWaitEvent(s, R->last, 0));
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
@@ -959,6 +1016,9 @@ fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *c
 // first, each into the first launch with room
 fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solver_ctl *ctl, int serial)
 {
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    ResidentDevice *R = resident_device();
+    if (!R) return fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
     std::vector<std::unique_ptr<ResidentBatch>> batches;
     std::vector<int> order(idx);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return g.cs[a]->d.res_G > g.cs[b]->d.res_G; });
@@ -967,12 +1027,12 @@ fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solv
         bool placed = false;
         for (auto &b : batches) placed = placed || b->add(d.self, d);
         if (!placed) {
-            batches.emplace_back(new ResidentBatch());
+            batches.emplace_back(new ResidentBatch(R));
             batches.back()->add(d.self, d);
         }
     }
     for (auto &b : batches) {
-        fvm_status st = resident_launch(*b, ctl, serial, g.s);
+        fvm_status st = resident_launch(R, *b, ctl, serial, g.s);
         if (st != FVM_OK) return st;
     }
     return FVM_OK;
@@ -996,7 +1056,7 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
     if (kind == 1 && precond != FVM_PC_AMG && resident_usable())
         for (int i = 0; i < g.n(); ++i)
             if (fits(g.cs[i])) on.push_back(i);
-    if (on.empty()) return run_launched(g, kind, ctl_src, ctl, res);
+    if (on.empty() || (g.cs[0]->o.precision == FVM_MIXED && solo_in_flight())) return run_launched(g, kind, ctl_src, ctl, res);
     const int serial = resident_serial();
     if (g.cs[0]->o.precision == FVM_MIXED) {
         // the recurrence starts from the launched solve's start
@@ -1269,13 +1329,15 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
 {
     const int n = g.n();
     Phase ph("whole-step launch");
+    std::unique_ptr<SoloMark> mark(n_steps > 0 ? new SoloMark(n, g.s) : nullptr);
     if (n_steps > 0) launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s);
     HIPCHK(hipGetLastError());
     std::vector<KState> res;
     int32_t all = FVM_OK;
     if (n_steps > 0) {
-        fvm_status st = snapshot(g, res);
+        fvm_status st = snapshot(g, res);   // waits for the launch
         if (st != FVM_OK) return st;
+        mark.reset();
     }
     bool failed = false;
     for (int i = 0; i < n; ++i) {
@@ -1377,24 +1439,31 @@ extern "C" fvm_status solve_pressure(fvm_case *c, const double *gamma, const dou
 }
 
 namespace {
-// bytes of the static scratch a case's reduction slots, tickets, Krylov
-// states and descriptor copy take (256-byte aligned sections)
+// bytes of the static scratch a case's reduction slots, tickets and Krylov
+// states take (256-byte aligned sections); the descriptor copy, the group
+// tickets' lines and the resident solve's slots lie behind them, in a part
+// sized for any case that fits otherwise
 size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
 {
-    size_t off = 0;
+    size_t off = 0, behind = kStaticScratchBytes;
     auto take = [&](size_t bytes) {
         unsigned char *a = base ? base + off : nullptr;
         off += (bytes + 255) / 256 * 256;
         return a;
     };
-    unsigned char *self = take(sizeof(DevCase));
+    auto take_behind = [&](size_t bytes) {
+        unsigned char *a = base ? base + behind : nullptr;
+        behind += (bytes + 255) / 256 * 256;
+        return a;
+    };
     unsigned char *p1 = take(sizeof(double) * (size_t)kMaxRed * d.red_stride);
     unsigned char *p2 = take(sizeof(double) * (size_t)kMaxRed * d.red_stride2);
-    unsigned char *gt = take(sizeof(unsigned int) * (size_t)d.red_stride2 * kTicketStep);
     unsigned char *tk = take(sizeof(unsigned int) * 64);
     unsigned char *ks = take(sizeof(KState) * kNumKs);
-    unsigned char *rs = d.res_G > 0 ? take(sizeof(double) * (size_t)std::max(1, d.res_words)) : nullptr;
-    unsigned char *rg = d.res_G > 0 ? take(sizeof(int32_t)) : nullptr;
+    unsigned char *self = take_behind(sizeof(DevCase));
+    unsigned char *gt = take_behind(sizeof(unsigned int) * (size_t)d.red_stride2 * kTicketStep);
+    unsigned char *rs = d.res_G > 0 ? take_behind(sizeof(double) * (size_t)std::max(1, d.res_words)) : nullptr;
+    unsigned char *rg = d.res_G > 0 ? take_behind(sizeof(int32_t)) : nullptr;
     if (h) {
         h->res_slots = reinterpret_cast<double *>(rs);
         h->res_gen = reinterpret_cast<int32_t *>(rg);
@@ -1406,7 +1475,7 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
         h->ks = reinterpret_cast<KState *>(ks);
         h->ks_gather = nullptr;
     }
-    return off;
+    return behind <= kStaticScratchBytes + kStaticBehindBytes ? off : SIZE_MAX;
 }
 }  // namespace
 
@@ -1451,12 +1520,16 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     KState ks{};
     bool launched = true;
     if (d.res_G > 0 && !d.dstar && resident_usable()) {
-        ResidentBatch rb;
-        rb.add(h.self, h);
         launch_res_reset(bs, 0, s);
         const int serial = resident_serial();
-        fvm_status st = resident_launch(rb, ctl, serial, s);
-        if (st != FVM_OK) return st;
+        {
+            std::lock_guard<std::mutex> lk(g_res_mu);
+            ResidentDevice *R = resident_device();
+            ResidentBatch rb(R);
+            rb.add(h.self, h);
+            fvm_status st = R ? resident_launch(R, rb, ctl, serial, s) : fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
+            if (st != FVM_OK) return st;
+        }
         KState all[kNumKs];
         HIPCHK(hipMemcpyAsync(all, h.ks, sizeof(all), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));

@@ -46,7 +46,7 @@ constexpr int kResMaxSum = 4;         // sums per reduction (slots laid out)
 #endif
 // words of a generation of slots: the parts' own sums, then the group sums,
 // a copy for each reading group
-RES_HD inline size_t res_gen_words(int ngrp) { return (size_t)kResMaxSum * (ngrp * kResGroup + kResGroups * kResGroups); }
+RES_HD inline constexpr size_t res_gen_words(int ngrp) { return (size_t)kResMaxSum * (ngrp * kResGroup + kResGroups * kResGroups); }
 // the same for the mixed-precision solve (resident_rr.h): parts of four
 // tiles of 1024 cells in order, groups of 16 parts (64 tiles), two sums
 constexpr int kRrTile = 1024;
@@ -365,6 +365,11 @@ void launch_clear_reduction(const BatchSet &bs, hipStream_t s);   // partials at
 // device's address of the array (looked up once per device), or NULL with
 // the HIP error code in *hip_err
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
+// descriptor, group tickets (683 groups at most), resident slots
+constexpr size_t kStaticBehindBytes = (size_t)256 << 10;
+static_assert(sizeof(DevCase) + 256 + kStaticScratchBytes / (sizeof(double) * kMaxRed * kGroup) * 4 * kTicketStep +
+                      sizeof(double) * kResGens * res_gen_words(kResGroups) + 512 <= kStaticBehindBytes,
+              "the part behind the counted sections holds any case");
 void *static_scratch(int *hip_err);
 void launch_set_patch(const BatchSet &bs, int patch, double u0, double u1, double u2, double pv, hipStream_t s);
 

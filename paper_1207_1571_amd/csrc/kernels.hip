@@ -4788,7 +4788,7 @@ void launch_clear_reduction(const BatchSet &bs, hipStream_t s) { run(k_clear_red
 // array at its own address, fetched once per device with that device
 // current; host code uses that address, never the array's name.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticBehindBytes];
 
 void *static_scratch(int *hip_err)
 {

@@ -272,3 +272,47 @@ def test_dic_cases_sharing_launches():
     for k, (c, a) in enumerate(zip(cases, alone)):
         for x, y in zip(c.get_state_numpy(), a):
             assert np.linalg.norm(x - y) <= TOL * np.linalg.norm(y), k
+
+
+def test_beside_whole_step_launches():
+    """While whole-step launches hold CUs, resident solves are spread over the
+    rest (or, in mixed precision, run as launched iterations): the same bits,
+    a case of 256 parts included, which has to wait for them."""
+    import torch
+    from paper_1207_1571_amd import fvm
+    small = [_case((12, 12, 12), k).with_(precision=wl.MIXED) for k in range(9)]
+    specs = [_case((60, 50, 50)), _case((40, 40, 40)).with_(precision=wl.MIXED), _case((128, 96, 84)),
+             _case((40, 36, 30), 3).with_(p_ctl=wl.SolverCtl(1e-9, precond=wl.PC_DIC))]
+    inputs = [_inputs(s.mesh, 8) for s in specs]
+    cases = [fvm.Case(s) for s in specs]
+
+    def solve(k):
+        g, r, p = (torch.from_numpy(a.copy()).cuda() for a in inputs[k])
+        cases[k].solve_pressure(g, r, p, 1e-12, max_iter=30, precond=specs[k].p_ctl.precond)
+        return p.cpu().numpy()
+
+    ref = [solve(k) for k in range(len(specs))]
+    stop, err, runs = threading.Event(), [], []
+
+    def work():
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                cs = [fvm.Case(m, stream=s) for m in small]
+                while not stop.is_set():
+                    fvm.piso_batch(cs, 4)
+                    runs.append(1)
+        except Exception as e:   # noqa: BLE001
+            err.append(e)
+
+    t = threading.Thread(target=work)
+    t.start()
+    try:
+        for _ in range(10):
+            for k in range(len(specs)):
+                assert np.array_equal(solve(k), ref[k]), k
+    finally:
+        stop.set()
+        t.join()
+    assert not err, err
+    assert runs
