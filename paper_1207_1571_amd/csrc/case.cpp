@@ -855,6 +855,7 @@ struct ResidentDevice {
     hipEvent_t last = nullptr; // recorded after the latest launch
     bool any = false;
     int solo = 0;              // CUs per XCD that whole-step launches in flight hold
+    std::vector<hipEvent_t> solo_end;   // recorded after each of them
 };
 std::mutex g_res_mu;
 ResidentDevice g_res_dev[64];
@@ -903,19 +904,28 @@ bool resident_usable()
 // small ones' steps.
 struct SoloMark {
     ResidentDevice *R = nullptr;
+    hipEvent_t end = nullptr;
     int cus = 0;
-    SoloMark(int n, hipStream_t s) : cus((n + kResGroups - 1) / kResGroups)
+    template <class F>
+    SoloMark(int n, hipStream_t s, F &&launch) : cus((n + kResGroups - 1) / kResGroups)
     {
         std::lock_guard<std::mutex> lk(g_res_mu);
         R = resident_device();
+        if (R && hipEventCreateWithFlags(&end, hipEventDisableTiming) != hipSuccess) R = nullptr, end = nullptr;
+        if (R && R->any) (void)hipStreamWaitEvent(s, R->last, 0);
+        launch();
         if (!R) return;
+        (void)hipEventRecord(end, s);
         R->solo += cus;
-        if (R->any) (void)hipStreamWaitEvent(s, R->last, 0);
+        R->solo_end.push_back(end);
     }
     ~SoloMark()
     {
         std::lock_guard<std::mutex> lk(g_res_mu);
-        if (R) R->solo -= cus;
+        if (!R) return;
+        R->solo -= cus;
+        R->solo_end.erase(std::find(R->solo_end.begin(), R->solo_end.end(), end));
+        (void)hipEventDestroy(end);
     }
     SoloMark(const SoloMark &) = delete;
     SoloMark &operator=(const SoloMark &) = delete;
@@ -935,7 +945,7 @@ bool solo_in_flight()
 // While whole-step launches hold CUs (room < kResGroup left per XCD), a case
 // whose groups do not fit on the rest, but whose parts do, is spread over
 // the XCDs (the sums are the same, only slower); a larger one takes all CUs
-// and waits for those held.
+// and starts behind the launches that hold them.
 struct ResidentBatch {
     BatchSet bs;
     int fill[kResGroups] = {};
@@ -998,6 +1008,8 @@ struct ResidentBatch {
 fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s)
 {
     if (R->any) HIPCHK(hipStreamWaitEvent(s, R->last, 0));
+    if (rb.full)
+        for (hipEvent_t e : R->solo_end) HIPCHK(hipStreamWaitEvent(s, e, 0));
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
@@ -1329,8 +1341,8 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
 {
     const int n = g.n();
     Phase ph("whole-step launch");
-    std::unique_ptr<SoloMark> mark(n_steps > 0 ? new SoloMark(n, g.s) : nullptr);
-    if (n_steps > 0) launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s);
+    std::unique_ptr<SoloMark> mark;
+    if (n_steps > 0) mark.reset(new SoloMark(n, g.s, [&] { launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s); }));
     HIPCHK(hipGetLastError());
     std::vector<KState> res;
     int32_t all = FVM_OK;
