@@ -3798,26 +3798,70 @@ __global__ void __launch_bounds__(kBlock) k_amg_cinv(const DevCase *dc)
     }
 }
 
+// ax + the off-diagonal part of row i, val(j) being neighbour j's value: the
+// owned faces, then the neighbour-side ones, each in order.  kAmgAhead faces'
+// loads are issued together: face by face, every term waits for a chain of
+// two to four loads (index, face, neighbour's values), and the level's
+// pointers were fetched again after the row's store.  On the 118k-row level
+// of 1M cells (16 faces a row) k_amg_down 20.1 -> 13.7 us, k_amg_up 21.5 -> 15.5.
+constexpr int kAmgAhead = 8;
+template <class V>
+__device__ __forceinline__ double amg_row(const AmgLevel &L, int i, double ax, V val)
+{
+    const auto *__restrict__ nei = gmem((const int32_t *)L.nei);
+    const auto *__restrict__ own = gmem((const int32_t *)L.own);
+    const auto *__restrict__ sort = gmem((const int32_t *)L.losort);
+    const auto *__restrict__ off = gmem((const double *)L.offd);
+    const int fb = gmem((const int32_t *)L.own_start)[i], fe = gmem((const int32_t *)L.own_start)[i + 1];
+    const int kb = gmem((const int32_t *)L.nbr_start)[i], ke = gmem((const int32_t *)L.nbr_start)[i + 1];
+    for (int f0 = fb; f0 < fe; f0 += kAmgAhead) {
+        int j[kAmgAhead];
+        double a[kAmgAhead], x[kAmgAhead];
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) {
+            const int f = min(f0 + u, fe - 1);
+            j[u] = nei[f];
+            a[u] = off[f];
+        }
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) x[u] = val(j[u]);
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u)
+            if (f0 + u < fe) ax += a[u] * x[u];
+    }
+    for (int k0 = kb; k0 < ke; k0 += kAmgAhead) {
+        int f[kAmgAhead], j[kAmgAhead];
+        double a[kAmgAhead], x[kAmgAhead];
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) f[u] = sort[min(k0 + u, ke - 1)];
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) {
+            j[u] = own[f[u]];
+            a[u] = off[f[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) x[u] = val(j[u]);
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u)
+            if (k0 + u < ke) ax += a[u] * x[u];
+    }
+    return ax;
+}
+
 // x = w b / diag and r = b - A x (neighbours' x from their b and diag)
 __global__ void __launch_bounds__(kBlock) k_amg_down(const DevCase *dc, int l)
 {
     const DevCase &d = *dc;
     if (d.ks[3].done) return;
-    const AmgLevel &L = d.amg[l];
+    const AmgLevel L = d.amg[l];
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= L.n) return;
-    const double bi = L.b[i], xi = kAmgOmega * bi / L.diag[i];
-    L.x[i] = xi;
-    double ax = L.diag[i] * xi;
-    for (int f = L.own_start[i]; f < L.own_start[i + 1]; ++f) {
-        const int j = L.nei[f];
-        ax += L.offd[f] * (kAmgOmega * L.b[j] / L.diag[j]);
-    }
-    for (int k = L.nbr_start[i]; k < L.nbr_start[i + 1]; ++k) {
-        const int f = L.losort[k], j = L.own[f];
-        ax += L.offd[f] * (kAmgOmega * L.b[j] / L.diag[j]);
-    }
-    L.r[i] = bi - ax;
+    const auto *__restrict__ b = gmem((const double *)L.b);
+    const auto *__restrict__ dg = gmem((const double *)L.diag);
+    const double bi = b[i], di = dg[i], xi = kAmgOmega * bi / di;
+    const double ax = amg_row(L, i, di * xi, [&](int j) { return kAmgOmega * b[j] / dg[j]; });
+    gmem(L.x)[i] = xi;
+    gmem(L.r)[i] = bi - ax;
 }
 
 // coarse right-hand side: sum of the fine residuals over each aggregate
@@ -3825,12 +3869,22 @@ __global__ void __launch_bounds__(kBlock) k_amg_restrict(const DevCase *dc, int 
 {
     const DevCase &d = *dc;
     if (d.ks[3].done) return;
-    const AmgLevel &C = d.amg[l], &F = d.amg[l - 1];
+    const AmgLevel C = d.amg[l];
+    const auto *__restrict__ r = gmem((const double *)d.amg[l - 1].r);
+    const auto *__restrict__ mem = gmem((const int32_t *)C.members);
     const int t = blockIdx.x * kBlock + threadIdx.x;
     if (t >= C.n) return;
+    const int kb = gmem((const int32_t *)C.mstart)[t], ke = gmem((const int32_t *)C.mstart)[t + 1];
     double a = 0.0;
-    for (int k = C.mstart[t]; k < C.mstart[t + 1]; ++k) a += F.r[C.members[k]];
-    C.b[t] = a;
+    for (int k0 = kb; k0 < ke; k0 += kAmgAhead) {
+        double v[kAmgAhead];
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u) v[u] = r[mem[min(k0 + u, ke - 1)]];
+#pragma unroll
+        for (int u = 0; u < kAmgAhead; ++u)
+            if (k0 + u < ke) a += v[u];
+    }
+    gmem(C.b)[t] = a;
 }
 
 // coarsest level: out = A^-1 b
@@ -3852,21 +3906,15 @@ __global__ void __launch_bounds__(kBlock) k_amg_up(const DevCase *dc, int l)
 {
     const DevCase &d = *dc;
     if (d.ks[3].done) return;
-    const AmgLevel &L = d.amg[l];
-    const double *__restrict__ xc = d.amg[l + 1].out;
+    const AmgLevel L = d.amg[l];
+    const auto *__restrict__ xc = gmem((const double *)d.amg[l + 1].out);
+    const auto *__restrict__ x = gmem((const double *)L.x);
+    const auto *__restrict__ agg = gmem((const int32_t *)L.agg);
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= L.n) return;
-    const double xi = L.x[i] + xc[L.agg[i]];
-    double ax = L.diag[i] * xi;
-    for (int f = L.own_start[i]; f < L.own_start[i + 1]; ++f) {
-        const int j = L.nei[f];
-        ax += L.offd[f] * (L.x[j] + xc[L.agg[j]]);
-    }
-    for (int k = L.nbr_start[i]; k < L.nbr_start[i + 1]; ++k) {
-        const int f = L.losort[k], j = L.own[f];
-        ax += L.offd[f] * (L.x[j] + xc[L.agg[j]]);
-    }
-    L.out[i] = xi + kAmgOmega * (L.b[i] - ax) / L.diag[i];
+    const double xi = x[i] + xc[agg[i]], di = gmem((const double *)L.diag)[i];
+    const double ax = amg_row(L, i, di * xi, [&](int j) { return x[j] + xc[agg[j]]; });
+    gmem(L.out)[i] = xi + kAmgOmega * (gmem((const double *)L.b)[i] - ax) / di;
 }
 
 // Small coarse levels: a thread per row would walk its faces one dependent
