@@ -310,7 +310,10 @@ enum {
  *     the reference pin) into the layout; d_out its diagonal [n_cells]
  *     (LAP) or the layout's values [K * n_cells + n_crs], B slot-major (row
  *     i, slot k at k * n_cells + i) then C (HY_LAP).
- *   SPMV: d_in x [n_cells]; d_out A x with the matrix of the last LAP.
+ *   SPMV: d_in x [n_cells]; d_out A x with the pressure matrix assembled
+ *     last: by LAP, or since then by a pressure solve (solve_pressure, a
+ *     PISO or SIMPLE step: its last solve) or fvm_dic_apply.  Undefined
+ *     before any of these.
  *   HY_SPMV, HY_STMVP: d_in x; d_out A x or A^T x with the layout's values.
  *   HY_SETMAT: d_in [diag n_cells | upper n_int | lower n_int], upper / lower
  *     per caller internal face = the coefficient in the row of the caller's

@@ -387,6 +387,8 @@ struct fvm_case {
     std::vector<fvm_patch> patches;
     Poller poll;
     int last_iters[4] = {0, 0, 0, 0};   // momentum, pressure, momentum inner; chunk sizing
+    bool sell_stale = false;   // the pressure matrix was assembled anew and its sliced-ELL copy not (FP64): a resident
+                               // solve reads no such copy, FVM_OP_SPMV has to make it
     // whole PISO steps in one workgroup (see FVM_STEP_AUTO).  FP64 cases of
     // these sizes run launched phases around the resident pressure CG, which
     // spreads a case over several CUs: a step of 15 500 cells takes 1.2 ms
@@ -1078,6 +1080,7 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
         launch_set_ctl(bs, 3, 1, ctl_src, ctl ? ctl->tol : 0.0, ctl ? ctl->rel_tol : 0.0, ctl ? ctl->max_iter : 0, g.s);
         launch_rr_resident_start(bs, g.s);
     }
+    for (int i : on) g.cs[i]->sell_stale = true;
     fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial);
     if (st != FVM_OK) return st;
     if ((int)on.size() < g.n()) {
@@ -1124,7 +1127,10 @@ fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *c
         max_iter = std::max<long>(max_iter, ctl_src == 2 ? ctl->max_iter : kind == 0 ? c->o.u_ctl.max_iter : c->o.p_ctl.max_iter);
     launch_set_ctl(bs, first, count, ctl_src, ctl ? ctl->tol : 0.0, ctl ? ctl->rel_tol : 0.0, ctl ? ctl->max_iter : 0, s);
     if (kind == 0) launch_bicg_init(bs, c0->o.u_solver == FVM_SOLVER_BICGSTAB, s);
-    else launch_pcg_init(bs, pc, s);
+    else {
+        launch_pcg_init(bs, pc, s);
+        for (auto *c : g.cs) c->sell_stale = false;
+    }
     fvm_status st;
     if (!mixed) {
         if (dic) launch_dic_precond(bs, 1, s);
@@ -1533,6 +1539,7 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     bool launched = true;
     if (d.res_G > 0 && !d.dstar && resident_usable()) {
         launch_res_reset(bs, 0, s);
+        c->sell_stale = true;
         const int serial = resident_serial();
         {
             std::lock_guard<std::mutex> lk(g_res_mu);
@@ -1552,6 +1559,7 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     if (launched) {
         launch_set_ctl(bs, 3, 1, 2, ctl->tol, ctl->rel_tol, ctl->max_iter, s);
         launch_pcg_init(bs, 0, s);
+        c->sell_stale = false;
     }
     // direct launches in chunks, the stop flag read back after each chunk
     // (iterations past it return at once); no graph, no pinned buffer
@@ -1583,6 +1591,7 @@ extern "C" fvm_status fvm_dic_apply(fvm_case *c, const double *gamma, const doub
     const Group g(c, s);
     const DevCase &d = c->d;
     launch_p_system_from_gamma(g.bs, gamma, r, s);
+    c->sell_stale = true;
     HIPCHK(hipMemcpyAsync(d.r, r, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     launch_dic_reset(g.bs, s);
     launch_dic_precond(g.bs, 1, s);
@@ -1602,6 +1611,8 @@ extern "C" fvm_status fvm_case_operator(fvm_case *c, int32_t op, const double *d
     if (!d_in || (op != FVM_OP_HY_SETMAT && !d_out)) return fvm_fail(FVM_EINVAL, "operator: null array");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Group g(c, s);
+    if (op == FVM_OP_SPMV && c->sell_stale) launch_sell_fill(g.bs, s);
+    if (op == FVM_OP_SPMV || op == FVM_OP_LAP) c->sell_stale = false;
     launch_operator(g.bs, op, d_in, d_out, s);
     HIPCHK(hipGetLastError());
     return FVM_OK;

@@ -403,6 +403,7 @@ void launch_bicg_iter(const BatchSet &bs, hipStream_t s);
 // Krylov: momentum BiCGStab on the three components (FP64)
 void launch_bicgstab_iter(const BatchSet &bs, hipStream_t s);
 // Krylov: pressure CG (FP64), Jacobi or DIC
+void launch_sell_fill(const BatchSet &bs, hipStream_t s);   // pressure matrix values into the sliced-ELL copy
 void launch_pcg_init(const BatchSet &bs, int dic, hipStream_t s);
 void launch_pcg_iter(const BatchSet &bs, int dic, int parity, hipStream_t s);   // parity: iteration index & 1
 void launch_bicg_fallback(const BatchSet &bs, hipStream_t s);   // restart kStatusFallback components as FP64 BiCG

@@ -4475,9 +4475,11 @@ bool sell_w6(const BatchSet &bs)
 constexpr int kSpmvGrid = SZ_CELL4;
 constexpr int kWideDirCells = 4 << 20;   // 2048 blocks of 8 x 256 cells
 
+void launch_sell_fill(const BatchSet &bs, hipStream_t s) { run(k_sell_fill, bs, SZ_CELL, s); }
+
 void launch_pcg_init(const BatchSet &bs, int dic, hipStream_t s)
 {
-    run(k_sell_fill, bs, SZ_CELL, s);
+    launch_sell_fill(bs, s);
     run(k_pcg_sumx, bs, SZ_CELL, s);
     run(k_pcg_init, bs, SZ_CELL, s, dic);
 }
