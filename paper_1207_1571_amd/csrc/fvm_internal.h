@@ -4,6 +4,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -174,8 +175,11 @@ struct fvm_mesh {
     // per thread on: slots (-c, -b, -1, +1, +b, +c), b and c even, lower
     // slots mirrored from the upper ones, every neighbour inside the mesh
     int32_t sell_n7 = 0;
-    mutable std::shared_ptr<AmgHost> amg;   // AMG hierarchy, built on first use
-    mutable std::shared_ptr<PartsHost> parts, tile_parts, level_parts;   // parts of the resident CG, built on first use
+    // built on first use, under cache_mu (cases of one mesh may be created on
+    // several threads), and kept unchanged while the mesh exists
+    mutable std::mutex cache_mu;
+    mutable std::shared_ptr<AmgHost> amg;                                // AMG hierarchy
+    mutable std::shared_ptr<PartsHost> parts, tile_parts, level_parts;   // parts of the resident CG
 };
 
 // ---------------------------------------------------------------------------

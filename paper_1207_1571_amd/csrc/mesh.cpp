@@ -246,6 +246,7 @@ void face_ranges(int32_t n, const std::vector<int32_t> &own, const std::vector<i
 
 const AmgHost &mesh_amg(const fvm_mesh &m)
 {
+    std::lock_guard<std::mutex> lk(m.cache_mu);
     if (m.amg) return *m.amg;
     auto h = std::make_shared<AmgHost>();
     h->L.emplace_back();
@@ -616,6 +617,7 @@ bool fill_parts(const fvm_mesh &m, PartsHost &h, const std::vector<int32_t> &par
 
 const PartsHost &mesh_parts(const fvm_mesh &m)
 {
+    std::lock_guard<std::mutex> lk(m.cache_mu);
     if (m.parts) return *m.parts;
     auto h = std::make_shared<PartsHost>();
     const int32_t N = m.N;
@@ -676,6 +678,7 @@ const PartsHost &mesh_parts(const fvm_mesh &m)
 
 const PartsHost &mesh_level_parts(const fvm_mesh &m)
 {
+    std::lock_guard<std::mutex> lk(m.cache_mu);
     if (m.level_parts) return *m.level_parts;
     auto h = std::make_shared<PartsHost>();
     const int32_t N = m.N, G = (N + kResCells - 1) / kResCells, W = m.sell_W <= 4 ? 4 : 6;
@@ -729,6 +732,7 @@ const PartsHost &mesh_level_parts(const fvm_mesh &m)
 
 const PartsHost &mesh_tile_parts(const fvm_mesh &m)
 {
+    std::lock_guard<std::mutex> lk(m.cache_mu);
     if (m.tile_parts) return *m.tile_parts;
     auto h = std::make_shared<PartsHost>();
     const int32_t N = m.N, G = (N + kResCells - 1) / kResCells;
