@@ -42,6 +42,12 @@ fvm_status fvm_fail(fvm_status code, const std::string &msg)
     return code;
 }
 
+// end of a C entry point whose body is a try block: nothing is thrown past it
+// (the messages are short enough to be stored without an allocation)
+#define C_ENTRY_END                                                          \
+    catch (const std::bad_alloc &) { return fvm_fail(FVM_ENOMEM, "out of memory"); } \
+    catch (...) { return fvm_fail(FVM_EDEVICE, "host error"); }
+
 extern "C" const char *fvm_last_error(void) { return fvm_err_buf().c_str(); }
 
 #define HIPCHK(x)                                                                                   \
@@ -104,7 +110,7 @@ void prof_end(const char *cls, hipStream_t s)
 }
 
 extern "C" fvm_status fvm_profile_enable(int32_t on)
-{
+try {
     std::lock_guard<std::mutex> g(g_prof_mu);
     if (on) {
         for (auto &kv : g_prof) prof_resolve(kv.second);
@@ -113,9 +119,10 @@ extern "C" fvm_status fvm_profile_enable(int32_t on)
     g_prof_on = on != 0;
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" fvm_status fvm_profile_read(const char *cls, double *total_ms, int64_t *launches)
-{
+try {
     std::lock_guard<std::mutex> g(g_prof_mu);
     auto it = g_prof.find(cls ? cls : "");
     double ms = 0.0;
@@ -129,6 +136,7 @@ extern "C" fvm_status fvm_profile_read(const char *cls, double *total_ms, int64_
     if (launches) *launches = n;
     return FVM_OK;
 }
+C_ENTRY_END
 
 // ---------------------------------------------------------------------------
 // workspace planning: the same walk sizes the workspace and assigns pointers
@@ -480,7 +488,7 @@ struct Phase {
 // public: workspace size, create, destroy
 // ---------------------------------------------------------------------------
 extern "C" fvm_status fvm_case_workspace_bytes(const fvm_mesh *m, const fvm_case_opts *o, size_t *bytes)
-{
+try {
     fvm_status st = check_opts(m, o);
     if (st != FVM_OK) return st;
     if (!bytes) return fvm_fail(FVM_EINVAL, "case: null output");
@@ -490,6 +498,7 @@ extern "C" fvm_status fvm_case_workspace_bytes(const fvm_mesh *m, const fvm_case
     *bytes = b.off;
     return FVM_OK;
 }
+C_ENTRY_END
 
 namespace {
 template <class T>
@@ -502,19 +511,23 @@ hipError_t up(T *dst, const std::vector<T> &src, hipStream_t s)
 
 extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o, void *ws, size_t bytes, void *stream,
                                       fvm_case **out)
-{
+try {
     if (!out) return fvm_fail(FVM_EINVAL, "case: null output");
     *out = nullptr;
     fvm_status st = check_opts(m, o);
     if (st != FVM_OK) return st;
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255)) return fvm_fail(FVM_EINVAL, "case: workspace must be 256-byte aligned");
     size_t need = 0;
-    fvm_case_workspace_bytes(m, o, &need);
+    st = fvm_case_workspace_bytes(m, o, &need);
+    if (st != FVM_OK) return st;
     if (bytes < need)
         return fvm_fail(FVM_ENOMEM, "case: workspace too small (" + std::to_string(bytes) + " < " + std::to_string(need) + ")");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    fvm_case *c = new (std::nothrow) fvm_case();
-    if (!c) return fvm_fail(FVM_ENOMEM, "case: out of host memory");
+    struct Release {
+        void operator()(fvm_case *k) const { fvm_case_destroy(k); }
+    };
+    std::unique_ptr<fvm_case, Release> owner(new fvm_case());   // released on every way out but the last
+    fvm_case *c = owner.get();
     c->o = *o;
     c->N = m->N; c->F = m->F; c->Fi = m->Fi; c->Fb = m->Fb; c->npatch = m->npatch;
     c->nonorth = m->nonorth; c->has_fixed_p = m->has_fixed_p;
@@ -522,13 +535,8 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     Bump b{reinterpret_cast<char *>(ws)};
     std::vector<AmgLevel> amg_lv;
     plan(*m, *o, b, c->d, &amg_lv);
-    auto fail = [&](fvm_status code) {
-        c->poll.release();
-        delete c;
-        return code;
-    };
     st = c->poll.init();
-    if (st != FVM_OK) return fail(st);
+    if (st != FVM_OK) return st;
     DevCase &d = c->d;
     const int np = c->npatch;
     std::vector<int32_t> uk(np), pk(np);
@@ -539,7 +547,7 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
         for (int k = 0; k < 3; ++k) uv[3 * p + k] = c->patches[p].u_value[k];
     }
     const size_t F = m->F;
-#define UPCHK(x) do { if ((x) != hipSuccess) return fail(fvm_fail(FVM_EDEVICE, "case: upload " #x)); } while (0)
+#define UPCHK(x) do { if ((x) != hipSuccess) return fvm_fail(FVM_EDEVICE, "case: upload " #x); } while (0)
     UPCHK(hipMemcpyAsync(d.self, &c->d, sizeof(DevCase), hipMemcpyHostToDevice, s));
     UPCHK(up(d.own, m->own, s)); UPCHK(up(d.nei, m->nei, s));
     UPCHK(up(d.own_start, m->own_start, s)); UPCHK(up(d.nbr_start, m->nbr_start, s)); UPCHK(up(d.losort, m->losort, s));
@@ -591,7 +599,7 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     if (d.amg_nl > 0) {
         const AmgHost &A = mesh_amg(*m);
         if (d.amg_nc > kAmgDenseMax)
-            return fail(fvm_fail(FVM_EINVAL, "case: AMG coarsening stalled above the dense coarsest size"));
+            return fvm_fail(FVM_EINVAL, "case: AMG coarsening stalled above the dense coarsest size");
         auto w = [](const int32_t *p) { return const_cast<int32_t *>(p); };
         for (int l = 0; l < d.amg_nl; ++l) {
             const AmgLevelHost &L = A.L[l];
@@ -612,7 +620,7 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     if (d.hy_K > 0) {
         build_hybrid(*m, d.hy_K, hy);
         if (hy.nC != d.hy_nC || (int64_t)d.hy_K * m->N + hy.nC >= INT32_MAX)
-            return fail(fvm_fail(FVM_EINVAL, "case: hybrid layout too large for int32 positions"));
+            return fvm_fail(FVM_EINVAL, "case: hybrid layout too large for int32 positions");
         UPCHK(up(d.hy_I, hy.dI, s)); UPCHK(up(d.hy_J, hy.dJ, s)); UPCHK(up(d.hy_dpos, hy.dpos, s));
         UPCHK(up(d.hy_locO, hy.locO, s)); UPCHK(up(d.hy_locN, hy.locN, s));
         UPCHK(up(d.hy_cstart, hy.c_start, s)); UPCHK(up(d.hy_ccol, hy.c_col, s)); UPCHK(up(d.hy_ctrpos, hy.c_trpos, s));
@@ -635,9 +643,10 @@ extern "C" fvm_status fvm_case_create(const fvm_mesh *m, const fvm_case_opts *o,
     UPCHK(hipGetLastError());
     UPCHK(hipStreamSynchronize(s));   // host vectors above are temporaries
 #undef UPCHK
-    *out = c;
+    *out = owner.release();
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" void fvm_case_destroy(fvm_case *c)
 {
@@ -650,7 +659,7 @@ extern "C" void fvm_case_destroy(fvm_case *c)
 // public: state exchange
 // ---------------------------------------------------------------------------
 extern "C" fvm_status fvm_case_set_state(fvm_case *c, const double *U, const double *p, const double *phi, void *stream)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "case: null handle");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Group g(c, s);
@@ -661,9 +670,10 @@ extern "C" fvm_status fvm_case_set_state(fvm_case *c, const double *U, const dou
     HIPCHK(hipGetLastError());
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" fvm_status fvm_case_get_state(const fvm_case *c, double *U, double *p, double *phi, void *stream)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "case: null handle");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Group g(const_cast<fvm_case *>(c), s);
@@ -673,10 +683,11 @@ extern "C" fvm_status fvm_case_get_state(const fvm_case *c, double *U, double *p
     HIPCHK(hipGetLastError());
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" fvm_status fvm_case_set_patch_value(fvm_case *c, int32_t patch, const double u_value[3], double p_value,
                                                void *stream)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "case: null handle");
     if (patch < 0 || patch >= c->npatch || !u_value) return fvm_fail(FVM_EINVAL, "case: bad patch index");
     for (int k = 0; k < 3; ++k) c->patches[patch].u_value[k] = u_value[k];
@@ -687,6 +698,7 @@ extern "C" fvm_status fvm_case_set_patch_value(fvm_case *c, int32_t patch, const
     HIPCHK(hipGetLastError());
     return FVM_OK;
 }
+C_ENTRY_END
 
 // ---------------------------------------------------------------------------
 // Krylov drivers (over a group of cases)
@@ -1387,14 +1399,15 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
 }  // namespace
 
 extern "C" fvm_status piso_step(fvm_case *c, int32_t n_steps, void *stream, fvm_step_info *last)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "piso: null handle");
     return piso_step_batch(&c, 1, n_steps, stream, last);
 }
+C_ENTRY_END
 
 extern "C" fvm_status simple_iterate(fvm_case *c, int32_t max_iters, double res_tol, void *stream, int32_t *iters_done,
                                      fvm_step_info *last)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "simple: null handle");
     if (max_iters < 0) return fvm_fail(FVM_EINVAL, "simple: max_iters < 0");
     if (!(c->o.alpha_u > 0.0 && c->o.alpha_u <= 1.0) || !(c->o.alpha_p > 0.0 && c->o.alpha_p <= 1.0))
@@ -1425,10 +1438,11 @@ extern "C" fvm_status simple_iterate(fvm_case *c, int32_t max_iters, double res_
     if (last) *last = info[0];
     return acc;
 }
+C_ENTRY_END
 
 extern "C" fvm_status solve_pressure(fvm_case *c, const double *gamma, const double *rhs, double *p,
                                      const fvm_solver_ctl *ctl, void *stream, fvm_solve_info *out)
-{
+try {
     if (!c || !gamma || !rhs || !p || !ctl) return fvm_fail(FVM_EINVAL, "solve_pressure: null argument");
     if (ctl->precond != FVM_PC_JACOBI && ctl->precond != FVM_PC_DIC && ctl->precond != FVM_PC_AMG)
         return fvm_fail(FVM_EINVAL, "solve_pressure: bad preconditioner");
@@ -1455,6 +1469,7 @@ extern "C" fvm_status solve_pressure(fvm_case *c, const double *gamma, const dou
     if (ks.status < 0) return fvm_fail(ks.status, "solve_pressure: non-finite value or breakdown");
     return ks.status;
 }
+C_ENTRY_END
 
 namespace {
 // bytes of the static scratch a case's reduction slots, tickets and Krylov
@@ -1499,7 +1514,7 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
 
 extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, const double *rhs, double *p,
                                             const fvm_solver_ctl *ctl, void *stream, fvm_solve_info *out)
-{
+try {
     if (!c || !gamma || !rhs || !p || !ctl) return fvm_fail(FVM_EINVAL, "solve_pressure_static: null argument");
     if (ctl->precond != FVM_PC_JACOBI)
         return fvm_fail(FVM_EINVAL, "solve_pressure_static: Jacobi preconditioning only");
@@ -1581,10 +1596,11 @@ extern "C" fvm_status solve_pressure_static(fvm_case *c, const double *gamma, co
     if (ks.status < 0) return fvm_fail(ks.status, "solve_pressure_static: non-finite value or breakdown");
     return ks.status;
 }
+C_ENTRY_END
 
 extern "C" fvm_status fvm_dic_apply(fvm_case *c, const double *gamma, const double *r, double *z, double *dstar,
                                     void *stream)
-{
+try {
     if (!c || !gamma || !r || !z) return fvm_fail(FVM_EINVAL, "dic_apply: null argument");
     if (!c->d.dstar) return fvm_fail(FVM_EINVAL, "dic_apply: case was not created with the DIC preconditioner");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -1600,9 +1616,10 @@ extern "C" fvm_status fvm_dic_apply(fvm_case *c, const double *gamma, const doub
     HIPCHK(hipStreamSynchronize(s));
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" fvm_status fvm_case_operator(fvm_case *c, int32_t op, const double *d_in, double *d_out, void *stream)
-{
+try {
     if (!c) return fvm_fail(FVM_EINVAL, "operator: null case");
     if (op < FVM_OP_GRAD || op > FVM_OP_HY_SETMAT) return fvm_fail(FVM_EINVAL, "operator: unknown op");
     if (op >= FVM_OP_HY_GRAD && c->d.hy_K <= 0)
@@ -1617,10 +1634,11 @@ extern "C" fvm_status fvm_case_operator(fvm_case *c, int32_t op, const double *d
     HIPCHK(hipGetLastError());
     return FVM_OK;
 }
+C_ENTRY_END
 
 extern "C" fvm_status piso_step_batch(fvm_case *const *cases, int32_t n, int32_t n_steps, void *stream,
                                       fvm_step_info *infos)
-{
+try {
     if (!cases || n < 1 || n > kMaxBatch) return fvm_fail(FVM_EINVAL, "batch: need 1 <= n_cases <= 32");
     if (n_steps < 0) return fvm_fail(FVM_EINVAL, "piso: n_steps < 0");
     for (int i = 0; i < n; ++i) {
@@ -1690,3 +1708,4 @@ extern "C" fvm_status piso_step_batch(fvm_case *const *cases, int32_t n, int32_t
     if (all < 0) return fvm_fail(all, "piso: a solve failed (non-finite value or breakdown); the case was rolled back");
     return all;
 }
+C_ENTRY_END
