@@ -189,7 +189,7 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
                 for (int k = 0; k < NV; ++k)
                     gst(all + (k * kResGroups + lane) * kResGroups + tm.grp, slot_word(t[k]));
         }
-        bool same_xcd = FIRST && tm.size * t[NV > 2 ? 2 : 0] == t[NV > 1 ? 1 : 0] * t[NV > 1 ? 1 : 0];
+        bool same_xcd = FIRST && one && tm.size * t[NV > 2 ? 2 : 0] == t[NV > 1 ? 1 : 0] * t[NV > 1 ? 1 : 0];
         if (!one && ok) {
             ok = poll_slots<NV>(all + tm.grp * kResGroups, kResGroups * kResGroups, tm.ngrp, tm.ticks, t);
             if (FIRST) {
