@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -861,15 +862,22 @@ void record_iters(Group &g, const std::vector<KState> &res, int first, int count
 
 // ---- resident pressure CG (resident_cg.h) ----
 // The workgroups of such a launch wait for each other, so all of them must
-// be on the device at once: a launch takes at most one per CU, and a launch
-// waits (on the device) for the one before it on the same device, on
-// whichever stream and from whichever thread that was enqueued.
+// be on the device at once.  A launch takes at most one per CU, and the host
+// keeps account of the CUs that the launches in flight may hold: it starts a
+// launch beside them where the CUs suffice, else (on the device) behind the
+// oldest of them, whichever stream and thread those came from.  CUs are
+// counted per XCD, the same number on all eight: workgroup b of a launch runs
+// on XCD (b + c) % 8, c differing from launch to launch.
+struct InFlight {
+    hipEvent_t end;   // recorded behind the launch
+    hipStream_t s;
+    int cus;          // CUs of an XCD it may hold
+    bool solo;        // a whole-step launch
+};
 struct ResidentDevice {
-    int usable = -1;           // -1: not looked at yet
-    hipEvent_t last = nullptr; // recorded after the latest launch
-    bool any = false;
-    int solo = 0;              // CUs per XCD that whole-step launches in flight hold
-    std::vector<hipEvent_t> solo_end;   // recorded after each of them
+    int usable = -1;                // -1: not looked at yet
+    std::vector<InFlight> flight;   // in the order of their launches
+    std::vector<hipEvent_t> idle;   // events for the next ones
 };
 std::mutex g_res_mu;
 ResidentDevice g_res_dev[64];
@@ -888,7 +896,7 @@ ResidentDevice *resident_device()
     if (R.usable < 0) {
         int cus = 0;
         R.usable = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= kResParts &&
-                   res_prepare() == 0 && hipEventCreateWithFlags(&R.last, hipEventDisableTiming) == hipSuccess;
+                   res_prepare() == 0;
         (void)hipGetLastError();
     }
     return R.usable ? &R : nullptr;
@@ -909,41 +917,82 @@ bool resident_usable()
     return resident_device() != nullptr;
 }
 
-// A whole-step launch of n cases on stream s, until it is destroyed (after
-// the launch has ended).  Such a launch holds its CUs for many steps, up to
-// seconds: it starts behind the resident launch in flight, whose workgroups
-// it could otherwise keep off the device, and resident launches keep clear
-// of it meanwhile.  Without that a stream of mixed-precision requests of all
-// sizes took 51 s, its large cases waiting inside their launches for the
-// small ones' steps.
-struct SoloMark {
+// The launches of one call in the account, until the call has waited for them.
+struct LaunchMark {
     ResidentDevice *R = nullptr;
-    hipEvent_t end = nullptr;
-    int cus = 0;
-    template <class F>
-    SoloMark(int n, hipStream_t s, F &&launch) : cus((n + kResGroups - 1) / kResGroups)
+    std::vector<hipEvent_t> mine;
+    LaunchMark() = default;
+    LaunchMark(const LaunchMark &) = delete;
+    LaunchMark &operator=(const LaunchMark &) = delete;
+    ~LaunchMark() { clear(); }
+    // the launch just enqueued on s (g_res_mu held)
+    fvm_status add(ResidentDevice *dev, hipStream_t s, int cus, bool solo)
     {
-        std::lock_guard<std::mutex> lk(g_res_mu);
-        R = resident_device();
-        if (R && hipEventCreateWithFlags(&end, hipEventDisableTiming) != hipSuccess) R = nullptr, end = nullptr;
-        if (R && R->any) (void)hipStreamWaitEvent(s, R->last, 0);
-        launch();
-        if (!R) return;
-        (void)hipEventRecord(end, s);
-        R->solo += cus;
-        R->solo_end.push_back(end);
+        R = dev;
+        hipEvent_t e = nullptr;
+        mine.reserve(mine.size() + 1);
+        R->flight.reserve(R->flight.size() + 1);
+        R->idle.reserve(R->idle.size() + R->flight.size() + 1);
+        if (!R->idle.empty()) {
+            e = R->idle.back();
+            R->idle.pop_back();
+        } else HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        R->flight.push_back(InFlight{e, s, cus, solo});
+        mine.push_back(e);
+        HIPCHK(hipEventRecord(e, s));
+        return FVM_OK;
     }
-    ~SoloMark()
+    // they have ended; at most 16 events are kept for later launches
+    void clear()
     {
+        if (mine.empty()) return;
         std::lock_guard<std::mutex> lk(g_res_mu);
-        if (!R) return;
-        R->solo -= cus;
-        R->solo_end.erase(std::find(R->solo_end.begin(), R->solo_end.end(), end));
-        (void)hipEventDestroy(end);
+        for (hipEvent_t e : mine) {
+            R->flight.erase(std::find_if(R->flight.begin(), R->flight.end(), [e](const InFlight &f) { return f.end == e; }));
+            if (R->idle.size() < 16) R->idle.push_back(e);
+            else (void)hipEventDestroy(e);
+        }
+        mine.clear();
     }
-    SoloMark(const SoloMark &) = delete;
-    SoloMark &operator=(const SoloMark &) = delete;
 };
+
+// launches in flight that a launch on s does not follow anyway (the
+// per-thread stream has one handle for all threads)
+std::vector<InFlight> beside(const ResidentDevice *R, hipStream_t s)
+{
+    std::vector<InFlight> v;
+    for (const InFlight &f : R->flight)
+        if (f.s != s || s == hipStreamPerThread) v.push_back(f);
+    return v;
+}
+
+// A whole-step launch of n cases on stream s.  Such a launch holds its CUs
+// for many steps, up to seconds: where the CUs do not suffice for both, it
+// starts behind the resident launches in flight, whose workgroups it could
+// otherwise keep off the device, and resident launches keep clear of it.
+// Without that a stream of mixed-precision requests of all sizes took 51 s,
+// its large cases waiting inside their launches for the small ones' steps.
+template <class F>
+fvm_status solo_launch(int n, hipStream_t s, LaunchMark &mark, F &&launch)
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    ResidentDevice *R = resident_device();
+    const int cus = (n + kResGroups - 1) / kResGroups;
+    if (R) {
+        int room = kResGroup;
+        const std::vector<InFlight> others = beside(R, s);
+        for (const InFlight &f : others) room -= f.cus;
+        for (const InFlight &f : others) {
+            if (room >= cus) break;
+            if (f.solo) continue;
+            HIPCHK(hipStreamWaitEvent(s, f.end, 0));
+            room += f.cus;
+        }
+    }
+    launch();
+    HIPCHK(hipGetLastError());
+    return R ? mark.add(R, s, cus, true) : FVM_OK;
+}
 
 // whole-step launches are in flight: mixed solves, whose launched iterations
 // give the same bits, then run as these
@@ -951,38 +1000,37 @@ bool solo_in_flight()
 {
     std::lock_guard<std::mutex> lk(g_res_mu);
     const ResidentDevice *R = resident_device();
-    return R && R->solo > 0;
+    return R && std::any_of(R->flight.begin(), R->flight.end(), [](const InFlight &f) { return f.solo; });
 }
 
-// cases that share a launch, and which part each workgroup holds: workgroup
-// 8 k + x runs on XCD x, so a group of parts takes workgroups of one x.
-// While whole-step launches hold CUs (room < kResGroup left per XCD), a case
-// whose groups do not fit on the rest, but whose parts do, is spread over
-// the XCDs (the sums are the same, only slower); a larger one takes all CUs
-// and starts behind the launches that hold them.
+// Cases that share a launch, and which part each workgroup holds: the
+// workgroups 8 k + x run on one XCD, so a group of parts takes workgroups of
+// one x.  At most `room` workgroups go to an XCD.
 struct ResidentBatch {
     BatchSet bs;
     int fill[kResGroups] = {};
     uint8_t cs[kResParts], pt[kResParts];
     int room;
-    bool full = false;
-    explicit ResidentBatch(const ResidentDevice *R) : room(std::max(0, kResGroup - (R ? R->solo : 0)))
+    std::vector<hipEvent_t> behind;   // launches it starts behind
+    explicit ResidentBatch(int room_) : room(std::max(0, room_))
     {
         bs.n = 0;
         std::memset(cs, 255, sizeof(cs));
         std::memset(pt, 0, sizeof(pt));
     }
-    // false when the case's groups do not fit beside what is there
-    bool add(const DevCase *self, const DevCase &d)
+    // false when the case's groups do not fit beside what is there; with
+    // `spread` a case whose parts fit is placed over all XCDs then (the sums
+    // are the same, only slower)
+    bool add(const DevCase *self, const DevCase &d, bool spread = false)
     {
         const int G = d.res_G;
         const bool mixed = d.f_x != nullptr;
         if (bs.n > 0 && bs.host[0]->res_W != d.res_W) return false;
         auto group = [&](int part) { return mixed ? part / kRrGroup : res_group_of(part, G); };
-        if (full) return false;
-        // the XCD of every group: the fullest one that still has room
+        // the XCD of every group: the fullest one that still has room (a
+        // part by itself, which shares no L2 with others: the emptiest)
         int at[kRrGroups];
-        auto groups_fit = [&](int limit) {
+        auto groups_fit = [&] {
             int sum[kResGroups];
             std::copy(fill, fill + kResGroups, sum);
             for (int part = 0; part < G;) {
@@ -991,22 +1039,17 @@ struct ResidentBatch {
                 while (part < G && group(part) == g) ++part, ++size;
                 at[g] = -1;
                 for (int x = 0; x < kResGroups; ++x)
-                    if (sum[x] + size <= limit && (at[g] < 0 || sum[x] > sum[at[g]])) at[g] = x;
+                    if (sum[x] + size <= room && (at[g] < 0 || (G == 1 ? sum[x] < sum[at[g]] : sum[x] > sum[at[g]]))) at[g] = x;
                 if (at[g] < 0) return false;
                 sum[at[g]] += size;
             }
             return true;
         };
-        bool spread = false;
-        if (!groups_fit(room)) {
+        if (!groups_fit()) {
             int left = 0;
             for (int x = 0; x < kResGroups; ++x) left += room - fill[x];
-            spread = room < kResGroup && left >= G;
-            if (!spread) {
-                if (bs.n > 0 || !groups_fit(kResGroup)) return false;
-                full = room < kResGroup;
-            }
-        }
+            if (!spread || left < G) return false;
+        } else spread = false;
         for (int part = 0; part < G; ++part) {
             const int x = spread ? (int)(std::min_element(fill, fill + kResGroups) - fill) : at[group(part)];
             const int b = kResGroups * fill[x]++ + x;
@@ -1016,14 +1059,50 @@ struct ResidentBatch {
         batch_add(bs, self, &d);
         return true;
     }
+    int cus() const { return *std::max_element(fill, fill + kResGroups); }
 };
 
-// (g_res_mu held)
-fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s)
+// A new launch on s that holds the case (g_res_mu held): beside what is in
+// flight where the case fits there; else behind the oldest resident launches,
+// as many as make room; else spread over what whole-step launches leave; else
+// behind all.  A part by itself waits for no other workgroup: it never starts
+// behind anything.
+std::unique_ptr<ResidentBatch> resident_batch(const ResidentDevice *R, const DevCase *self, const DevCase &d, hipStream_t s)
 {
-    if (R->any) HIPCHK(hipStreamWaitEvent(s, R->last, 0));
-    if (rb.full)
-        for (hipEvent_t e : R->solo_end) HIPCHK(hipStreamWaitEvent(s, e, 0));
+    std::vector<InFlight> res = beside(R, s), solo;
+    std::copy_if(res.begin(), res.end(), std::back_inserter(solo), [](const InFlight &f) { return f.solo; });
+    res.erase(std::remove_if(res.begin(), res.end(), [](const InFlight &f) { return f.solo; }), res.end());
+    int room = kResGroup, room_solo;
+    for (const InFlight &f : solo) room -= f.cus;
+    room_solo = room;
+    for (const InFlight &f : res) room -= f.cus;
+    const bool alone = d.res_G == 1;
+    std::vector<hipEvent_t> behind;
+    std::unique_ptr<ResidentBatch> b;
+    for (size_t k = 0;; ++k) {
+        b.reset(new ResidentBatch(room));
+        if (b->add(self, d)) break;
+        if (k < res.size() && !alone) {
+            behind.push_back(res[k].end);
+            room += res[k].cus;
+            continue;
+        }
+        b.reset(new ResidentBatch(alone ? kResGroup : room_solo));
+        if (b->add(self, d, true)) break;
+        for (const InFlight &f : solo) behind.push_back(f.end);
+        b.reset(new ResidentBatch(kResGroup));
+        (void)b->add(self, d);   // any case fits on the whole device
+        break;
+    }
+    b->behind = std::move(behind);
+    return b;
+}
+
+// (g_res_mu held)
+fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s,
+                           LaunchMark &mark)
+{
+    for (hipEvent_t e : rb.behind) HIPCHK(hipStreamWaitEvent(s, e, 0));
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
@@ -1031,16 +1110,14 @@ fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solve
     else if (rb.bs.host[0]->f_x) launch_res_rr(rb.bs, rb.cs, rb.pt, t_res_ticks, serial, s);
     else launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipEventRecord(R->last, s));
-    R->any = true;
-    return FVM_OK;
+    return mark.add(R, s, rb.cus(), false);
 }
 
 fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res);
 
 // the cases `idx` of the group (all resident), packed into launches: largest
 // first, each into the first launch with room
-fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solver_ctl *ctl, int serial)
+fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solver_ctl *ctl, int serial, LaunchMark &mark)
 {
     std::lock_guard<std::mutex> lk(g_res_mu);
     ResidentDevice *R = resident_device();
@@ -1052,13 +1129,10 @@ fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solv
         const DevCase &d = g.cs[i]->d;
         bool placed = false;
         for (auto &b : batches) placed = placed || b->add(d.self, d);
-        if (!placed) {
-            batches.emplace_back(new ResidentBatch(R));
-            batches.back()->add(d.self, d);
-        }
+        if (!placed) batches.push_back(resident_batch(R, d.self, d, g.s));
     }
     for (auto &b : batches) {
-        fvm_status st = resident_launch(R, *b, ctl, serial, g.s);
+        fvm_status st = resident_launch(R, *b, ctl, serial, g.s, mark);
         if (st != FVM_OK) return st;
     }
     return FVM_OK;
@@ -1093,7 +1167,8 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
         launch_rr_resident_start(bs, g.s);
     }
     for (int i : on) g.cs[i]->sell_stale = true;
-    fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial);
+    LaunchMark mark;
+    fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial, mark);
     if (st != FVM_OK) return st;
     if ((int)on.size() < g.n()) {
         if (!g.rest) {
@@ -1105,8 +1180,9 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
         st = run_launched(*g.rest, kind, ctl_src, ctl, res);
         if (st != FVM_OK) return st;
     }
-    st = snapshot(g, res);
+    st = snapshot(g, res);   // waits for the launches
     if (st != FVM_OK) return st;
+    mark.clear();
     std::vector<fvm_case *> late;
     for (int i : on)
         if (res[(size_t)i * kNumKs + kNumKs - 1].pad[0]) late.push_back(g.cs[i]);
@@ -1359,15 +1435,17 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
 {
     const int n = g.n();
     Phase ph("whole-step launch");
-    std::unique_ptr<SoloMark> mark;
-    if (n_steps > 0) mark.reset(new SoloMark(n, g.s, [&] { launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s); }));
-    HIPCHK(hipGetLastError());
+    LaunchMark mark;
+    if (n_steps > 0) {
+        fvm_status st = solo_launch(n, g.s, mark, [&] { launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s); });
+        if (st != FVM_OK) return st;
+    }
     std::vector<KState> res;
     int32_t all = FVM_OK;
     if (n_steps > 0) {
         fvm_status st = snapshot(g, res);   // waits for the launch
         if (st != FVM_OK) return st;
-        mark.reset();
+        mark.clear();
     }
     bool failed = false;
     for (int i = 0; i < n; ++i) {
@@ -1556,17 +1634,18 @@ try {
         launch_res_reset(bs, 0, s);
         c->sell_stale = true;
         const int serial = resident_serial();
+        LaunchMark mark;
         {
             std::lock_guard<std::mutex> lk(g_res_mu);
             ResidentDevice *R = resident_device();
-            ResidentBatch rb(R);
-            rb.add(h.self, h);
-            fvm_status st = R ? resident_launch(R, rb, ctl, serial, s) : fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
+            if (!R) return fvm_fail(FVM_EDEVICE, "solve: resident kernel not usable");
+            fvm_status st = resident_launch(R, *resident_batch(R, h.self, h, s), ctl, serial, s, mark);
             if (st != FVM_OK) return st;
         }
         KState all[kNumKs];
         HIPCHK(hipMemcpyAsync(all, h.ks, sizeof(all), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        mark.clear();
         launched = all[kNumKs - 1].pad[0] != 0;   // a wait ran out: begin again
         if (launched) launch_res_reset(bs, serial, s);
         else ks = all[3];

@@ -22,8 +22,8 @@
 //   reduction 2             stop test, beta; every z is visible after it
 //
 // Every workgroup of a case must be on the device at once: a launch has at
-// most one per CU, and the host lets no two such launches overlap (case.cpp,
-// resident_launch).  Should other work keep a workgroup from starting all
+// most one per CU, and the host starts it beside other launches only where
+// the CUs suffice for all of them (case.cpp, resident_batch).  Should other work keep a workgroup from starting all
 // the same (another process on the card), the waits end after a time limit:
 // whoever waited marks the solve and leaves, and the host runs the launched
 // iterations from the saved start value instead.

@@ -1,0 +1,96 @@
+"""Resident pressure solves on several streams: launches share the device where
+the CUs suffice, wait for each other where they do not, and give the bits that
+each gives alone.
+"""
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1207_1571_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(shape):
+    return wl.duct(shape, mode="piso", dt=0.01) if shape[1] == 1 else wl.cavity(shape, Re=100.0, dt=0.01)
+
+
+def _inputs(mesh, seed):
+    rng = np.random.default_rng(seed)
+    rhs = rng.normal(size=mesh.n_cells)
+    return rng.uniform(0.5, 2.0, mesh.n_faces), rhs - rhs.mean(), rng.normal(size=mesh.n_cells) * 0.1
+
+
+class _Solver:
+    """A case on a stream of its own."""
+
+    def __init__(self, shape, seed):
+        import torch
+        from paper_1207_1571_amd import fvm
+        self.stream = torch.cuda.Stream()
+        with torch.cuda.stream(self.stream):
+            spec = _case(shape)
+            self.case = fvm.Case(spec, stream=self.stream)
+            self.g, self.r, self.p0 = (torch.from_numpy(a).cuda() for a in _inputs(spec.mesh, seed))
+        self.stream.synchronize()
+
+    def solve(self, max_iter):
+        """max_iter iterations (the tolerance is out of reach)"""
+        import torch
+        with torch.cuda.stream(self.stream):
+            p = self.p0.clone()
+            st, info = self.case.solve_pressure(self.g, self.r, p, 0.0, max_iter=max_iter)
+            assert st == 1 and info["iters"] == max_iter
+            return p.cpu().numpy()
+
+
+# one part (a workgroup that waits for nobody); one group of 4 parts
+@pytest.mark.parametrize("cells", [4096, 16384])
+def test_small_solves_run_side_by_side(cells):
+    """While one stream runs solves of 4000 iterations (a rod, which takes as
+    many to converge), another ends many of 20 in the time of each."""
+    long, short = _Solver((cells, 1, 1), 1), _Solver((cells, 1, 1), 2)
+    ref, long_ref = short.solve(20), long.solve(4000)
+    runs, err, started = 20, [], threading.Event()
+
+    def work():
+        try:
+            for _ in range(runs):
+                started.set()
+                assert np.array_equal(long.solve(4000), long_ref)
+        except BaseException as e:   # noqa: BLE001
+            err.append(e)
+
+    t = threading.Thread(target=work)
+    t.start()
+    started.wait()
+    n = 0
+    while t.is_alive():
+        assert np.array_equal(short.solve(20), ref)
+        n += 1
+    t.join()
+    print(f"[streams] {cells} cells: {n} short solves beside {runs} long ones", file=sys.stderr, flush=True)
+    assert not err, err
+    assert n >= 3 * runs, n
+
+
+def test_solves_of_all_sizes_on_many_streams():
+    """More CUs asked for than there are: one to 256 parts on six streams."""
+    shapes = [(128, 96, 84), (16, 16, 16), (64, 64, 40), (24, 24, 24), (60, 50, 50), (12, 12, 12)]
+    solvers = [_Solver(s, k) for k, s in enumerate(shapes)]
+    ref = [s.solve(40) for s in solvers]
+    err = []
+
+    def work(k):
+        try:
+            for _ in range(12):
+                assert np.array_equal(solvers[k].solve(40), ref[k]), k
+        except BaseException as e:   # noqa: BLE001
+            err.append(e)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(len(solvers))]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert not err, err
