@@ -16,6 +16,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <iterator>
@@ -450,7 +451,8 @@ struct Group {
     Poller *poll;
     hipStream_t s;
     std::shared_ptr<GraphCache> graphs = std::make_shared<GraphCache>();
-    std::shared_ptr<Group> rest;   // the cases whose pressure solve runs launched iterations, where others do not
+    std::shared_ptr<Group> rest;   // the cases whose pressure solve runs launched iterations, where others do not,
+    int rest_scope = 0;            // at this resident_scope()
     explicit Group(fvm_case *c, hipStream_t st) : poll(&c->poll), s(st)
     {
         cs.push_back(c);
@@ -876,16 +878,25 @@ struct InFlight {
 };
 struct ResidentDevice {
     int usable = -1;                // -1: not looked at yet
+    int late = 0;                   // launches in a row whose waits ran out
+    std::chrono::steady_clock::time_point again;   // no launch whose workgroups wait for each other before this
     std::vector<InFlight> flight;   // in the order of their launches
     std::vector<hipEvent_t> idle;   // events for the next ones
 };
 std::mutex g_res_mu;
 ResidentDevice g_res_dev[64];
 // limit of one wait between workgroups, in 10 ns: far above any wait behind
-// other kernels of this library
+// other kernels of this library (the first wait of a launch, which ends when
+// all its workgroups have started, has a limit of its own, kResStartTicks)
 constexpr long kResWaitTicks = 1000000000L;
+// A wait runs out where something outside this account holds CUs, as a rule
+// another process, which will go on doing so: launched iterations, which
+// share the card, then run for a minute, after each further launch whose
+// waits run out for twice as long, up to half an hour.
+constexpr std::chrono::seconds kResPause(60);
+constexpr int kResPauseDoublings = 5;
 thread_local long t_res_ticks = kResWaitTicks;
-thread_local bool t_res_leave_out = false;
+thread_local bool t_res_leave_out = false, t_res_forget = false;
 
 // state of the current device (g_res_mu held); nullptr when not usable
 ResidentDevice *resident_device()
@@ -911,10 +922,24 @@ int resident_serial()
     return serial;
 }
 
-bool resident_usable()
+// which resident solves the current device takes at present: 0 none, 1 those
+// of one part, whose workgroup waits for no other, 2 all
+int resident_scope()
 {
     std::lock_guard<std::mutex> lk(g_res_mu);
-    return resident_device() != nullptr;
+    const ResidentDevice *R = resident_device();
+    return !R ? 0 : R->late > 0 && std::chrono::steady_clock::now() < R->again ? 1 : 2;
+}
+
+// a launch whose workgroups wait for each other has ended
+void resident_outcome(bool late)
+{
+    if (t_res_forget) return;
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    ResidentDevice *R = resident_device();
+    if (!R) return;
+    if (late) R->again = std::chrono::steady_clock::now() + kResPause * (1 << std::min(R->late, kResPauseDoublings));
+    R->late = late ? R->late + 1 : 0;
 }
 
 // The launches of one call in the account, until the call has waited for them.
@@ -1147,15 +1172,16 @@ fvm_status resident_solves(Group &g, const std::vector<int> &idx, const fvm_solv
 fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res)
 {
     const int precond = ctl_src == 2 ? ctl->precond : g.cs[0]->o.p_ctl.precond;
+    const int scope = kind == 1 && precond != FVM_PC_AMG ? resident_scope() : 0;
     std::vector<int> on;
     // a DIC case's parts are in level order, for DIC solves; the others' serve
     // Jacobi solves
     auto fits = [&](const fvm_case *c) {
-        return c->d.res_G > 0 && precond == (c->d.dstar ? FVM_PC_DIC : FVM_PC_JACOBI);
+        return c->d.res_G > 0 && (scope == 2 || (scope == 1 && c->d.res_G == 1)) &&
+               precond == (c->d.dstar ? FVM_PC_DIC : FVM_PC_JACOBI);
     };
-    if (kind == 1 && precond != FVM_PC_AMG && resident_usable())
-        for (int i = 0; i < g.n(); ++i)
-            if (fits(g.cs[i])) on.push_back(i);
+    for (int i = 0; i < g.n(); ++i)
+        if (fits(g.cs[i])) on.push_back(i);
     if (on.empty() || (g.cs[0]->o.precision == FVM_MIXED && solo_in_flight())) return run_launched(g, kind, ctl_src, ctl, res);
     const int serial = resident_serial();
     if (g.cs[0]->o.precision == FVM_MIXED) {
@@ -1171,7 +1197,8 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
     fvm_status st = resident_solves(g, on, ctl_src == 2 ? ctl : nullptr, serial, mark);
     if (st != FVM_OK) return st;
     if ((int)on.size() < g.n()) {
-        if (!g.rest) {
+        if (!g.rest || g.rest_scope != scope) {
+            g.rest_scope = scope;
             std::vector<fvm_case *> off;
             for (auto *c : g.cs)
                 if (!fits(c)) off.push_back(c);
@@ -1186,6 +1213,7 @@ fvm_status run_solve(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl,
     std::vector<fvm_case *> late;
     for (int i : on)
         if (res[(size_t)i * kNumKs + kNumKs - 1].pad[0]) late.push_back(g.cs[i]);
+    if (std::any_of(on.begin(), on.end(), [&](int i) { return g.cs[i]->d.res_G > 1; })) resident_outcome(!late.empty());
     if (!late.empty()) {
         // a wait ran out: these solves begin again as launched iterations
         Group again(late.data(), (int)late.size(), g.poll, g.s);
@@ -1413,13 +1441,14 @@ fvm_status rollback_failed(Group &g, const std::vector<fvm_step_info> &info)
 
 }  // namespace
 
-// for tests of the path that begins a solve again: the calling thread's wait
-// limit (ticks <= 0: the usual one), and whether its resident launches leave
-// out the last workgroup, so that every other one waits until the limit
-extern "C" void fvm_resident_test_hook(long ticks, int leave_out)
+extern "C" void fvm_resident_test_hook(long ticks, int flags)
 {
     t_res_ticks = ticks > 0 ? ticks : kResWaitTicks;
-    t_res_leave_out = ticks > 0 && leave_out;
+    t_res_leave_out = ticks > 0 && (flags & 1);
+    t_res_forget = ticks > 0 && !(flags & 2);
+    if (ticks > 0) return;
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    if (ResidentDevice *R = resident_device()) R->late = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1630,7 +1659,8 @@ try {
     HIPCHK(hipMemcpyAsync(d.p, p, sizeof(double) * c->N, hipMemcpyDeviceToDevice, s));
     KState ks{};
     bool launched = true;
-    if (d.res_G > 0 && !d.dstar && resident_usable()) {
+    const int scope = d.dstar ? 0 : resident_scope();
+    if (d.res_G > 0 && (scope == 2 || (scope == 1 && d.res_G == 1))) {
         launch_res_reset(bs, 0, s);
         c->sell_stale = true;
         const int serial = resident_serial();
@@ -1647,6 +1677,7 @@ try {
         HIPCHK(hipStreamSynchronize(s));
         mark.clear();
         launched = all[kNumKs - 1].pad[0] != 0;   // a wait ran out: begin again
+        if (d.res_G > 1) resident_outcome(launched);
         if (launched) launch_res_reset(bs, serial, s);
         else ks = all[3];
     }

@@ -34,6 +34,10 @@
 
 constexpr int kResThreads = 512;
 constexpr int kResWaves = kResThreads / 64;
+// limit of the first wait, which ends when every part has started: a second.
+// The host starts a launch only where its account leaves the CUs free, so a
+// longer wait is for work it knows nothing of.
+constexpr long kResStartTicks = 100000000L;
 constexpr int kHaloStep = 5;   // halo cells a thread loads at once (a 16^3 brick's halo: 3 to 5 per thread)
 
 // value of one lane, in scalar registers
@@ -97,7 +101,7 @@ struct ResTeam {
     int part, G, gen;
     int grp, ngrp, first, size;   // group, groups, the group's first part and its parts
     bool local;
-    long ticks;      // limit of one wait (100 MHz clock)
+    long ticks, later;   // limit of one wait (100 MHz clock): at present, after the first reduction
 };
 
 // NV words at a + k * stride, polled by the wave until none is empty; false
@@ -214,6 +218,7 @@ __device__ __forceinline__ bool res_reduce(double (&v)[NV], ResTeam &tm, ResRed 
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] = sh.tot[par][k];
     tm.gen += 1;
+    if (FIRST) tm.ticks = tm.later;
     return !sh.late;
 }
 
@@ -456,7 +461,8 @@ __device__ __forceinline__ ResTeam res_team(const DevCase &d, int part, long tic
     tm.first = res_group_first(tm.grp, tm.G);
     tm.size = res_group_first(tm.grp + 1, tm.G) - tm.first;
     tm.local = false;
-    tm.ticks = ticks;
+    tm.ticks = min(ticks, kResStartTicks);
+    tm.later = ticks;
     return tm;
 }
 

@@ -104,6 +104,7 @@ __device__ __forceinline__ bool rr_reduce(double (&va)[NV], double (&vb)[NV], do
 #pragma unroll
     for (int k = 0; k < NV; ++k) out[k] = sh.tot[par][k];
     tm.gen += 1;
+    if (FIRST) tm.ticks = tm.later;
     return !sh.late;
 }
 
@@ -360,7 +361,8 @@ __global__ void __launch_bounds__(kResThreads) k_res_rr(Batch bt, ResMap map, in
     tm.first = tm.grp * kRrGroup;
     tm.size = min(kRrGroup, tm.G - tm.first);
     tm.local = false;
-    tm.ticks = ticks;
+    tm.ticks = min(ticks, kResStartTicks);
+    tm.later = ticks;
     const bool ok = rr_solve<W>(d, tm, serial, sh, rr_lds);
     res_end(d, tm, ok);
 }
