@@ -132,17 +132,18 @@ typedef struct {
     int32_t step_kernel;   /* FVM_STEP_AUTO or FVM_STEP_LAUNCHED (below) */
 } fvm_case_opts;
 
-/* How piso_step and piso_step_batch run a case.  FVM_STEP_AUTO: a small
- * mixed-precision case (at most 32 768 cells, at most 6 neighbours per cell,
- * orthogonal mesh, Jacobi pressure CG, BiCG momentum, at most 4 correctors,
- * no non-orthogonal correctors) runs its whole PISO steps, Krylov loops
- * included, in one workgroup of one kernel launch (many such cases side by
- * side, one per compute unit), since at that size launches and host round
- * trips per Krylov iteration would cost more than the arithmetic; any other
- * case, and every case under FVM_STEP_LAUNCHED, runs each phase as a
- * grid-wide launch (the FP64 Jacobi pressure CG of up to 1M cells as one
- * launch per solve).  Both give the method's result (they differ only in the
- * order of the floating-point sums). */
+/* How piso_step and piso_step_batch run a case.  FVM_STEP_AUTO: a small case
+ * (orthogonal mesh, Jacobi pressure CG, BiCG momentum, at most 4 correctors,
+ * no non-orthogonal correctors; at most 32 768 cells in mixed precision with
+ * at most 6 neighbours per cell, or at most 3 072 cells in either precision
+ * with more neighbours) runs its whole PISO steps, Krylov loops included, in
+ * one workgroup of one kernel launch (many such cases side by side, one per
+ * compute unit), since at that size launches and host round trips per Krylov
+ * iteration would cost more than the arithmetic; any other case, and every
+ * case under FVM_STEP_LAUNCHED, runs each phase as a grid-wide launch (a
+ * Jacobi or DIC pressure CG of up to 1M cells with at most 6 neighbours, in
+ * either precision, as one launch per solve).  Both give the method's result
+ * (they differ only in the order of the floating-point sums). */
 enum { FVM_STEP_AUTO = 0, FVM_STEP_LAUNCHED = 1 };
 
 typedef struct {
@@ -327,8 +328,9 @@ fvm_status fvm_case_operator(fvm_case *c, int32_t op, const double *d_in, double
 /* piso_step_batch -- advance several resident cases by n_steps PISO steps,
  * their kernels batched into shared launches (continuous-batching serving).
  * Every case must be FVM_MIXED or every case FVM_FP64.  When every case
- * qualifies for whole-step kernels (FVM_STEP_AUTO above), one launch runs
- * all n_steps steps of all cases, one workgroup per case, with no host
+ * qualifies for whole-step kernels (FVM_STEP_AUTO above), one launch (one
+ * more for cases with more than 6 neighbours per cell) runs all n_steps
+ * steps of all cases, one workgroup per case, with no host
  * round trip in between; otherwise every case runs launched phases.
  * infos[i] (may be NULL) receives case i's last-step record.  Each case's
  * result is the same as piso_step on it alone. */

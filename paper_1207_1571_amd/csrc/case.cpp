@@ -399,14 +399,18 @@ struct fvm_case {
     int last_iters[4] = {0, 0, 0, 0};   // momentum, pressure, momentum inner; chunk sizing
     bool sell_stale = false;   // the pressure matrix was assembled anew and its sliced-ELL copy not (FP64): a resident
                                // solve reads no such copy, FVM_OP_SPMV has to make it
-    // whole PISO steps in one workgroup (see FVM_STEP_AUTO).  FP64 cases of
-    // these sizes run launched phases around the resident pressure CG, which
-    // spreads a case over several CUs: a step of 15 500 cells takes 1.2 ms
-    // against 10.8 in one workgroup, one of 1 024 cells 1.2 against 2.4
+    bool wide() const { return d.sell_W > 6; }
+    // whole PISO steps in one workgroup (see FVM_STEP_AUTO).  FP64 cases with
+    // at most 6 neighbours per cell run launched phases around the resident
+    // pressure CG, which spreads a case over several CUs: a step of 15 500
+    // cells takes 1.2 ms against 10.8 in one workgroup, one of 1 024 cells 1.2
+    // against 2.4.  With more neighbours there is no resident CG: small cases
+    // keep their launch per call (kSoloWideCells).
     bool solo() const
     {
-        return o.step_kernel == FVM_STEP_AUTO && o.precision == FVM_MIXED && N <= kSoloMaxCells && d.sell_W <= 6 && !nonorth && o.n_non_orth_corr == 0 &&
-               o.n_corr <= kSoloMaxCorr && o.p_ctl.precond == FVM_PC_JACOBI && o.u_solver == FVM_SOLVER_BICG;
+        return o.step_kernel == FVM_STEP_AUTO && (wide() ? N <= kSoloWideCells : o.precision == FVM_MIXED && N <= kSoloMaxCells) &&
+               !nonorth && o.n_non_orth_corr == 0 && o.n_corr <= kSoloMaxCorr && o.p_ctl.precond == FVM_PC_JACOBI &&
+               o.u_solver == FVM_SOLVER_BICG;
     }
 };
 
@@ -1455,8 +1459,8 @@ extern "C" void fvm_resident_test_hook(long ticks, int flags)
 // public: PISO, SIMPLE, stand-alone pressure solve, batch
 // ---------------------------------------------------------------------------
 namespace {
-// n_steps PISO steps of every case of the group in one launch, one
-// workgroup per case; the kernel leaves each case's last-step record in its
+// n_steps PISO steps of every case of the group in one launch (a second one
+// for cases with more than 6 neighbours per cell), one workgroup per case; the kernel leaves each case's last-step record in its
 // Krylov state slots: 0..2 momentum, 3.. the pressure solves, the last one a
 // summary (iters: pressure solves recorded, status: worst over the steps,
 // done: steps completed, first: 1 when a step failed and was rolled back)
@@ -1465,8 +1469,13 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
     const int n = g.n();
     Phase ph("whole-step launch");
     LaunchMark mark;
-    if (n_steps > 0) {
-        fvm_status st = solo_launch(n, g.s, mark, [&] { launch_solo_piso(g.bs, n_steps, g.cs[0]->o.n_corr, g.s); });
+    for (const bool wide : {false, true}) {
+        BatchSet bs;
+        bs.n = 0;
+        for (auto *c : g.cs)
+            if (c->wide() == wide) batch_add(bs, c->d.self, &c->d);
+        if (n_steps < 1 || bs.n == 0) continue;
+        fvm_status st = solo_launch(bs.n, g.s, mark, [&] { launch_solo_piso(bs, n_steps, g.cs[0]->o.n_corr, g.s); });
         if (st != FVM_OK) return st;
     }
     std::vector<KState> res;

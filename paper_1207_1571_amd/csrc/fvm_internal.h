@@ -453,9 +453,15 @@ void launch_res_rr(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, lon
 // whole PISO steps, one workgroup per case (small orthogonal Jacobi/BiCG
 // cases, n_corr <= kSoloMaxCorr): grid = the batch's cases; the last
 // step's record is left in each case's Krylov state slots (see
-// k_solo_piso)
+// k_solo_piso).  Either every case has at most 6 neighbours per cell, or all
+// have more.
 void launch_solo_piso(const BatchSet &bs, int n_steps, int n_corr, hipStream_t s);
-constexpr int kSoloMaxCells = 1 << 15;
+constexpr int kSoloMaxCells = 1 << 15;   // mixed precision, at most 6 neighbours per cell
+// more neighbours, both precisions.  A step of hexagonal prisms in FP64, in
+// one workgroup / as launched iterations: 1000 cells 1.2 / 2.8 ms (32 cases
+// at once 1.3 / 4.4), 2744 cells 4.0 / 4.9 (4.4 / 6.7), 4096 cells 6.6 / 5.3
+// (7.2 / 7.6), 13 824 cells 33 / 9.3 (52 / 17).
+constexpr int kSoloWideCells = 3072;
 constexpr int kSoloMaxCorr = kNumKs - 4;
 void launch_rr_start(const BatchSet &bs, hipStream_t s);
 void launch_rr_iter(const BatchSet &bs, int parity, hipStream_t s);

@@ -2736,7 +2736,9 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
 // status over the steps, done: steps completed, first: 1 when a step failed
 // and was rolled back).  Scope (the host checks it): orthogonal meshes, at
 // most 4 pressure correctors without non-orthogonal correction, Jacobi CG
-// and BiCG, at most 6 neighbours per cell, mixed precision.
+// and BiCG; mixed precision with at most 6 neighbours per cell, its CG's
+// vectors on the chip, or more neighbours (which the resident solves have no
+// form for), its vectors in memory.
 // ---------------------------------------------------------------------------
 constexpr int kSolo = 512;
 constexpr int kSoloWaves = kSolo / 64;
@@ -2921,13 +2923,17 @@ __device__ void solo_bicg_iterate(const DevCase &d, SoloShared &sh, const BiArr<
     __syncthreads();
 }
 
-// momentum solve: FP64 refinement around restarted FP32 BiCG
-__device__ void solo_momentum(const DevCase &d, SoloShared &sh)
+// momentum solve: FP64 BiCG, or FP64 refinement around restarted FP32 BiCG
+__device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
 {
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) solo_ctl(d, sh.ks[c], 0);
     __syncthreads();
     solo_bicg_init(d, sh);
+    if (!mixed) {
+        solo_bicg_iterate<double>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
+        return;
+    }
     const long N = d.N;
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) solo_ctl(d, sh.ks[4 + c], 3);
@@ -3264,22 +3270,137 @@ __device__ bool solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s)
     return true;
 }
 
-// pressure solve of the assembled system (pdiag, poff, pb), x = p
-__device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp)
+// One iteration of a case with more than 6 neighbours per cell, in FP64 or
+// the FP32 recurrence with the FP64 solution (dir, product, update of the
+// launched kernels), its vectors in memory.  A round issues the loads of all
+// its cells before the first store (the arrays are not known to be distinct);
+// a thread takes cells i = tid, tid + kSolo, ... in that order.
+constexpr int kWideU = 4;
+template <class T>
+__device__ void solo_wide_iteration(const DevCase &d, SoloShared &sh, const CGArr<T> &v, KState &s)
+{
+    constexpr bool kMixed = sizeof(T) == 4;
+    const bool first = s.first;
+    const T beta = (T)s.beta;
+    const int N = d.N;
+    for (int b = (int)threadIdx.x; b < N; b += kSolo * kWideU) {
+        T rv[kWideU], dv[kWideU], pv[kWideU];
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) {
+            const int i = b + u * kSolo;
+            if (i < N) {
+                rv[u] = v.r[i];
+                dv[u] = v.diag[i];
+                pv[u] = first ? (T)0 : v.p[i];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) {
+            const int i = b + u * kSolo;
+            if (i < N) {
+                const T z = rv[u] / dv[u];
+                v.p[i] = first ? z : z + beta * pv[u];
+            }
+        }
+    }
+    __syncthreads();
+    double pq[1] = {0.0};
+    for (int b = (int)threadIdx.x; b < N; b += kSolo * 2) {
+        Row<T> rw[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = b + u * kSolo;
+            if (i < N) rw[u] = spmv_row<T, 0>(sell_view(d), v, i / kBlock, i);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = b + u * kSolo;
+            if (i < N) {
+                v.q[i] = rw[u].q;
+                pq[0] += rw[u].pq;
+            }
+        }
+    }
+    solo_sum<1>(pq, sh);
+    if (threadIdx.x == 0) {
+        if (!(pq[0] > 0.0) || !isfinite(pq[0])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
+        else s.alpha = s.rho / pq[0];
+    }
+    __syncthreads();
+    if (s.done) return;
+    const double al = s.alpha;
+    double acc[2] = {0.0, 0.0};
+    for (int b = (int)threadIdx.x; b < N; b += kSolo * kWideU) {
+        double xv[kWideU];
+        T pv[kWideU], rv[kWideU], qv[kWideU], dv[kWideU];
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) {
+            const int i = b + u * kSolo;
+            if (i < N) {
+                xv[u] = d.p[i];
+                pv[u] = v.p[i];
+                rv[u] = v.r[i];
+                qv[u] = v.q[i];
+                dv[u] = v.diag[i];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) {
+            const int i = b + u * kSolo;
+            if (i >= N) continue;
+            d.p[i] = xv[u] + al * (double)pv[u];
+            if (!kMixed) {
+                const double r = (double)rv[u] - al * (double)qv[u];
+                v.r[i] = (T)r;
+                acc[0] += fabs(r);
+                acc[1] += r * (r / (double)dv[u]);
+            } else {
+                const float ri = (float)rv[u] - (float)al * (float)qv[u];
+                v.r[i] = (T)ri;
+                acc[0] += fabs((double)ri);
+                acc[1] += (double)ri * (double)(ri / (float)dv[u]);
+            }
+        }
+    }
+    solo_sum<2>(acc, sh);
+    if (threadIdx.x == 0) {
+        s.iters += 1;
+        s.nres = acc[0] / s.nf;
+        s.first = 0;
+        if (kMixed) s.xbar = s.rho;   // rho of the previous iteration (for a replacement)
+        if (!isfinite(s.nres)) set_done(s, FVM_ENUMERIC);
+        else if (kMixed && (s.nres <= s.tol_eff || s.iters >= s.max_iter)) s.done = 2;   // verify on the true residual
+        else if (!kMixed && s.nres <= s.tol_eff) set_done(s, FVM_OK);
+        else if (!kMixed && s.iters >= s.max_iter) set_done(s, FVM_WARN_MAXITER);
+        else if (!(acc[1] > 0.0) || !isfinite(acc[1])) { set_done(s, FVM_ENUMERIC); s.iters += 1; }
+        else {
+            s.beta = acc[1] / s.rho;
+            s.rho = acc[1];
+        }
+    }
+    __syncthreads();
+}
+
+// pressure solve of the assembled system (pdiag, poff, pb), x = p; lp: the
+// LDS that holds p of the case (not for cases of the wide kernel)
+template <bool WIDE>
+__device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp, bool mixed)
 {
     KState &s = sh.ks[3];
     if (threadIdx.x == 0) solo_ctl(d, s, 1);
-    // sliced-ELL values (k_sell_fill) and the FP32 copies (k_mx_cvt)
+    // sliced-ELL values (k_sell_fill) and, mixed, the FP32 copies (k_mx_cvt)
     const int nsl = (d.N + kBlock - 1) / kBlock;
     SOLO_FOR(e, nsl * d.sell_W * kBlock) {
         const int fe = d.sell_fe[e];
         const double a = fe < 0 ? 0.0 : d.poff[fe >> 1];
-        d.f_sell_val[e] = (float)a;
+        if (mixed) d.f_sell_val[e] = (float)a;
+        else d.sell_val[e] = a;
     }
-    SOLO_FOR(t, d.N) {
-        d.f_pdiag[t] = (float)d.pdiag[t];
-        d.f_pexc[t] = (float)row_sum(d, t, d.pdiag, d.poff, d.poff);
-    }
+    if (mixed)
+        SOLO_FOR(t, d.N) {
+            d.f_pdiag[t] = (float)d.pdiag[t];
+            d.f_pexc[t] = (float)row_sum(d, t, d.pdiag, d.poff, d.poff);
+        }
     // start (k_pcg_sumx, k_pcg_init with Jacobi)
     double xb[1] = {0.0};
     SOLO_FOR(i, d.N) xb[0] += d.p[i];
@@ -3314,6 +3435,13 @@ __device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp)
         else s.rho = v[2];
     }
     __syncthreads();
+    if (WIDE && !mixed) {
+        const CGArr<double> a = cg_arrays<double>(d, 0);
+        for (long it = 0; it <= (long)d.p_max_iter && !s.done; ++it) solo_wide_iteration<double>(d, sh, a, s);
+        if (threadIdx.x == 0 && s.done != 1) set_done(s, FVM_ENUMERIC);
+        __syncthreads();
+        return;
+    }
     // k_rr_start: r32 = r64, rho = r32.(r32/diag32)
     if (!s.done) {
         double rho[1] = {0.0};
@@ -3330,7 +3458,17 @@ __device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp)
         }
         __syncthreads();
     }
-    if (d.N <= 8 * kSolo) solo_rr<8>(d, sh, s, lp);
+    if (WIDE) {
+        // a replacement check after every fourth iteration, as the launched
+        // driver enqueues them
+        constexpr int kReplaceEvery = 4;
+        const CGArr<float> a = cg_arrays<float>(d, 0);
+        const long limit = ((long)d.p_max_iter + 2) * kReplaceEvery;
+        for (long k = 0; k < limit && s.done != 1; ++k) {
+            if (!s.done) solo_wide_iteration<float>(d, sh, a, s);
+            if ((k + 1) % kReplaceEvery == 0) (void)solo_rr_replace(d, sh, s);
+        }
+    } else if (d.N <= 8 * kSolo) solo_rr<8>(d, sh, s, lp);
     else if (d.N <= 16 * kSolo) solo_rr<16>(d, sh, s, lp);
     else if (d.N <= 32 * kSolo) solo_rr<32>(d, sh, s, lp);
     else solo_rr<64>(d, sh, s, lp);
@@ -3344,7 +3482,10 @@ __device__ __forceinline__ void worst_status(int32_t &acc, int32_t s)
     else if (acc >= 0 && s > acc) acc = s;
 }
 
-// n_steps PISO steps of case blockIdx.x of the batch (orthogonal mesh)
+// n_steps PISO steps of case blockIdx.x of the batch (orthogonal mesh): mixed
+// precision and at most 6 neighbours per cell, or (WIDE) more neighbours and
+// either precision
+template <bool WIDE>
 __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int n_corr)
 {
     __shared__ SoloShared sh;
@@ -3362,6 +3503,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
         __syncthreads();
     }
     const DevCase &d = sdc;
+    const bool mixed = !WIDE || d.f_x != nullptr;
     const long N = d.N, F = d.F;
     int32_t worst = FVM_OK;
     int steps_done = 0, failed = 0, np = 0;
@@ -3378,7 +3520,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
         __syncthreads();
         SOLO_FOR(i, d.N) el_mom_cell(d, i, 0);
         __syncthreads();
-        solo_momentum(d, sh);
+        solo_momentum(d, sh, mixed);
         int32_t st = FVM_OK;
         for (int c = 0; c < 3; ++c) worst_status(st, sh.ks[c].status);
         if (threadIdx.x == 0)
@@ -3392,7 +3534,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
                 __syncthreads();
                 SOLO_FOR(i, d.N) el_p_cell(d, i, 1);
                 __syncthreads();
-                solo_pressure(d, sh, solo_p);
+                solo_pressure<WIDE>(d, sh, solo_p, mixed);
                 if (threadIdx.x == 0) sh.rec[3 + np] = sh.ks[3];
                 ++np;
                 worst_status(st, sh.ks[3].status);
@@ -4658,12 +4800,16 @@ void launch_solo_piso(const BatchSet &bs, int n_steps, int n_corr, hipStream_t s
 {
     Prof p("solo_piso", s);
     const Batch &b = bs.b[SZ_CELL];
+    if (bs.host[0]->sell_W > 6) {
+        hipLaunchKernelGGL(k_solo_piso<true>, dim3((unsigned)b.n), dim3(kSolo), 0, s, b, n_steps, n_corr);
+        return;
+    }
     int cells = 0;
     for (int c = 0; c < bs.n; ++c) cells = std::max(cells, bs.host[c]->N);
     const size_t lds = sizeof(float) * (size_t)cells;
-    (void)hipFuncSetAttribute((const void *)k_solo_piso, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)k_solo_piso<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(sizeof(float) * kSoloMaxCells));
-    hipLaunchKernelGGL(k_solo_piso, dim3((unsigned)b.n), dim3(kSolo), lds, s, b, n_steps, n_corr);
+    hipLaunchKernelGGL(k_solo_piso<false>, dim3((unsigned)b.n), dim3(kSolo), lds, s, b, n_steps, n_corr);
 }
 void launch_mx_inner_init(const BatchSet &bs, int, hipStream_t s) { run(k_mx_inner_init, bs, SZ_CELL, s); }
 void launch_mx_inner_iter(const BatchSet &bs, int, hipStream_t s)
