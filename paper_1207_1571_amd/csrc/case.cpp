@@ -882,6 +882,7 @@ struct InFlight {
 };
 struct ResidentDevice {
     int usable = -1;                // -1: not looked at yet
+    bool whole = false;             // it has the CUs the account assumes (not a partition of a card)
     int late = 0;                   // launches in a row whose waits ran out
     std::chrono::steady_clock::time_point again;   // no launch whose workgroups wait for each other before this
     std::vector<InFlight> flight;   // in the order of their launches
@@ -910,8 +911,8 @@ ResidentDevice *resident_device()
     ResidentDevice &R = g_res_dev[dev];
     if (R.usable < 0) {
         int cus = 0;
-        R.usable = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= kResParts &&
-                   res_prepare() == 0;
+        R.usable = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && res_prepare() == 0;
+        R.whole = cus >= kResParts;
         (void)hipGetLastError();
     }
     return R.usable ? &R : nullptr;
@@ -932,7 +933,7 @@ int resident_scope()
 {
     std::lock_guard<std::mutex> lk(g_res_mu);
     const ResidentDevice *R = resident_device();
-    return !R ? 0 : R->late > 0 && std::chrono::steady_clock::now() < R->again ? 1 : 2;
+    return !R ? 0 : !R->whole || (R->late > 0 && std::chrono::steady_clock::now() < R->again) ? 1 : 2;
 }
 
 // a launch whose workgroups wait for each other has ended
