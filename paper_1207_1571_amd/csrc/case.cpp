@@ -158,6 +158,18 @@ struct Bump {
     }
 };
 
+// the parts of the case's resident pressure solves; none for an AMG case,
+// whose own solves run launched (65 bytes per cell, and a third of the mesh
+// ingestion's host time)
+const PartsHost &case_parts(const fvm_mesh &m, const fvm_case_opts &o)
+{
+    static const PartsHost none;
+    return o.precision == FVM_MIXED           ? mesh_tile_parts(m)
+           : o.p_ctl.precond == FVM_PC_DIC    ? mesh_level_parts(m)
+           : o.p_ctl.precond == FVM_PC_JACOBI ? mesh_parts(m)
+                                              : none;
+}
+
 void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::vector<AmgLevel> *lv = nullptr)
 {
     const size_t N = m.N, F = m.F, Fi = m.Fi, Fb = m.Fb, np = m.npatch;
@@ -291,12 +303,12 @@ void plan(const fvm_mesh &m, const fvm_case_opts &o, Bump &b, DevCase &d, std::v
         d.hy_w = b.take<double>(E); d.hy_dl = b.take<double>(E); d.hy_g = b.take<double>(E); d.hy_phi = b.take<double>(E);
     }
     {
-        const PartsHost &P = mixed ? mesh_tile_parts(m) : dic ? mesh_level_parts(m) : mesh_parts(m);
+        const PartsHost &P = case_parts(m, o);
         d.res_G = P.G; d.res_W = P.W; d.res_n = P.n_max; d.res_local = P.local_max; d.res_halo_max = P.halo_max;
         if (P.G > 0) {
             d.res_start = b.take<int32_t>(P.start.size()); d.res_hstart = b.take<int32_t>(P.hstart.size());
             if (mixed) d.res_pub = b.take<uint8_t>(N);
-            else { d.res_far = b.take<int32_t>(P.far.size()); d.res_shown = b.take<int32_t>(P.shown.size()); }
+            else if (!dic) { d.res_far = b.take<int32_t>(P.far.size()); d.res_shown = b.take<int32_t>(P.shown.size()); }
             d.res_fin = b.take<int32_t>(P.G);
             d.res_cell = b.take<int32_t>(N); d.res_fe = b.take<int32_t>(P.fe.size());
             d.res_idx = b.take<uint16_t>(P.idx.size()); d.res_halo = b.take<int32_t>(P.halo.size());
@@ -596,9 +608,7 @@ try {
     UPCHK(up(d.sell_off, m->sell_off, s)); UPCHK(up(d.sell_mir, m->sell_mir, s));
     UPCHK(up(d.sell_fe, m->sell_fe, s)); UPCHK(up(d.sell_col, m->sell_col, s));
     if (d.res_G > 0) {
-        const PartsHost &P = o->precision == FVM_MIXED            ? mesh_tile_parts(*m)
-                             : o->p_ctl.precond == FVM_PC_DIC ? mesh_level_parts(*m)
-                                                              : mesh_parts(*m);
+        const PartsHost &P = case_parts(*m, *o);
         UPCHK(up(d.res_start, P.start, s)); UPCHK(up(d.res_hstart, P.hstart, s)); UPCHK(up(d.res_cell, P.cell, s));
         UPCHK(up(d.res_fe, P.fe, s)); UPCHK(up(d.res_idx, P.idx, s)); UPCHK(up(d.res_halo, P.halo, s));
         UPCHK(up(d.res_far, P.far, s)); UPCHK(up(d.res_shown, P.shown, s)); UPCHK(up(d.res_pub, P.pub, s));

@@ -690,8 +690,6 @@ const PartsHost &mesh_level_parts(const fvm_mesh &m)
         bisect(a.data(), N, G, size);
         h->start.assign(1, 0);
         h->cell.resize(N);
-        h->far.assign(G, 0);
-        h->shown.assign(G, 0);
         h->hstart.assign(1, 0);
         for (int32_t p = 0, at = 0; p < G; at += size[p++]) {
             std::sort(a.begin() + at, a.begin() + at + size[p], [](const PartCell &x, const PartCell &y) {
