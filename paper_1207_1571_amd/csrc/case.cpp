@@ -1599,10 +1599,10 @@ try {
 C_ENTRY_END
 
 namespace {
-// bytes of the static scratch a case's reduction slots, tickets and Krylov
-// states take (256-byte aligned sections); the descriptor copy, the group
-// tickets' lines and the resident solve's slots lie behind them, in a part
-// sized for any case that fits otherwise
+// sections of the static scratch, 256-byte aligned: a case's reduction slots,
+// tickets and Krylov states; the descriptor copy, the group tickets' lines and
+// the resident solve's slots lie behind the counted part, in one sized for any
+// case that is accepted.  Returns the bytes counted (static_counted_bytes).
 size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
 {
     size_t off = 0, behind = kStaticScratchBytes;
@@ -1635,7 +1635,8 @@ size_t static_layout(const DevCase &d, DevCase *h, unsigned char *base)
         h->ks = reinterpret_cast<KState *>(ks);
         h->ks_gather = nullptr;
     }
-    return behind <= kStaticScratchBytes + kStaticBehindBytes ? off : SIZE_MAX;
+    const size_t counted = static_counted_bytes(d.red_stride, d.red_stride2);
+    return off <= counted && behind <= kStaticScratchBytes + kStaticBehindBytes ? counted : SIZE_MAX;
 }
 }  // namespace
 

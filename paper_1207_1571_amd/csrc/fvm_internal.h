@@ -374,6 +374,15 @@ constexpr size_t kStaticBehindBytes = (size_t)256 << 10;
 static_assert(sizeof(DevCase) + 256 + kStaticScratchBytes / (sizeof(double) * kMaxRed * kGroup) * 4 * kTicketStep +
                       sizeof(double) * kResGens * res_gen_words(kResGroups) + 512 <= kStaticBehindBytes,
               "the part behind the counted sections holds any case");
+// bytes counted against kStaticScratchBytes: level-1 and level-2 slots,
+// tickets, states, and a descriptor and a word per group, so that the range of
+// accepted cases (up to 10 995 712 cells) does not move with what lies behind
+inline constexpr size_t static_counted_bytes(int32_t red_stride, int32_t red_stride2)
+{
+    constexpr auto section = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    return section(sizeof(double) * kMaxRed * red_stride) + section(sizeof(double) * kMaxRed * red_stride2) +
+           section(sizeof(unsigned int) * 64) + section(sizeof(KState) * kNumKs) + 1792 + section(sizeof(unsigned int) * red_stride2);
+}
 void *static_scratch(int *hip_err);
 void launch_set_patch(const BatchSet &bs, int patch, double u0, double u1, double u2, double pv, hipStream_t s);
 
