@@ -135,7 +135,7 @@ typedef struct {
 /* How piso_step and piso_step_batch run a case.  FVM_STEP_AUTO: a small case
  * (orthogonal mesh, Jacobi pressure CG, BiCG momentum, at most 4 correctors,
  * no non-orthogonal correctors; at most 32 768 cells in mixed precision with
- * at most 6 neighbours per cell, or at most 3 072 cells in either precision
+ * at most 6 neighbours per cell, or at most 4 096 cells in either precision
  * with more neighbours) runs its whole PISO steps, Krylov loops included, in
  * one workgroup of one kernel launch (many such cases side by side, one per
  * compute unit), since at that size launches and host round trips per Krylov

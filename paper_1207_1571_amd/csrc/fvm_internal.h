@@ -467,10 +467,10 @@ void launch_res_rr(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, lon
 void launch_solo_piso(const BatchSet &bs, int n_steps, int n_corr, hipStream_t s);
 constexpr int kSoloMaxCells = 1 << 15;   // mixed precision, at most 6 neighbours per cell
 // more neighbours, both precisions.  A step of hexagonal prisms in FP64, in
-// one workgroup / as launched iterations: 1000 cells 1.2 / 2.8 ms (32 cases
-// at once 1.3 / 4.4), 2744 cells 4.0 / 4.9 (4.4 / 6.7), 4096 cells 6.6 / 5.3
-// (7.2 / 7.6), 13 824 cells 33 / 9.3 (52 / 17).
-constexpr int kSoloWideCells = 3072;
+// one workgroup / as launched iterations: 1000 cells 1.1 / 2.8 ms (32 cases
+// at once 1.1 / 4.4), 2744 cells 3.4 / 4.9 (3.7 / 6.7), 4096 cells 5.4 / 5.3
+// (5.9 / 7.6; mixed precision 4.7 / 5.6), 8000 cells about 13 / 7.9.
+constexpr int kSoloWideCells = 4096;
 constexpr int kSoloMaxCorr = kNumKs - 4;
 void launch_rr_start(const BatchSet &bs, hipStream_t s);
 void launch_rr_iter(const BatchSet &bs, int parity, hipStream_t s);

@@ -2738,7 +2738,9 @@ __global__ void __launch_bounds__(kBlock) k_bicg_fallback(Batch bt)
 // most 4 pressure correctors without non-orthogonal correction, Jacobi CG
 // and BiCG; mixed precision with at most 6 neighbours per cell, its CG's
 // vectors on the chip, or more neighbours (which the resident solves have no
-// form for), its vectors in memory.
+// form for), its vectors in memory.  The two kernels share no function that is
+// not inlined (hence the parameter WIDE throughout): a call with the case's
+// state in registers cost 3.5 % of a step.
 // ---------------------------------------------------------------------------
 constexpr int kSolo = 512;
 constexpr int kSoloWaves = kSolo / 64;
@@ -2781,6 +2783,7 @@ __device__ __forceinline__ void solo_ctl(const DevCase &d, KState &s, int src)
 // ---- momentum: BiCG on the three components (k_bicg_* in one workgroup)
 
 // FP64 start (k_bicg_sumx, k_bicg_init): r = b - A x, r~ = r, n_f, rho
+template <bool WIDE>
 __device__ void solo_bicg_init(const DevCase &d, SoloShared &sh)
 {
     const long N = d.N;
@@ -2830,7 +2833,7 @@ __device__ void solo_bicg_init(const DevCase &d, SoloShared &sh)
 
 // BiCG iterations until the three systems (states ks0..ks0+2) are done;
 // at most `limit` iterations (the launched solver's bound)
-template <class T>
+template <class T, bool WIDE>
 __device__ void solo_bicg_iterate(const DevCase &d, SoloShared &sh, const BiArr<T> &v, int ks0, long limit)
 {
     const long N = d.N;
@@ -2924,14 +2927,15 @@ __device__ void solo_bicg_iterate(const DevCase &d, SoloShared &sh, const BiArr<
 }
 
 // momentum solve: FP64 BiCG, or FP64 refinement around restarted FP32 BiCG
+template <bool WIDE>
 __device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
 {
     if (threadIdx.x == 0)
         for (int c = 0; c < 3; ++c) solo_ctl(d, sh.ks[c], 0);
     __syncthreads();
-    solo_bicg_init(d, sh);
+    solo_bicg_init<WIDE>(d, sh);
     if (!mixed) {
-        solo_bicg_iterate<double>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
+        solo_bicg_iterate<double, WIDE>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
         return;
     }
     const long N = d.N;
@@ -2989,7 +2993,7 @@ __device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
                 else s.rho = v[3 + c];
             }
         __syncthreads();
-        solo_bicg_iterate<float>(d, sh, bi_arrays<float>(d), 4, (long)d.inner_max_iter + 1);
+        solo_bicg_iterate<float, WIDE>(d, sh, bi_arrays<float>(d), 4, (long)d.inner_max_iter + 1);
         // correction and outer residual (k_mx_correct, k_mx_resid)
         int keep[3];
         for (int c = 0; c < 3; ++c) keep[c] = act[c] && sh.ks[4 + c].status != FVM_ENUMERIC;
@@ -3053,7 +3057,7 @@ __device__ void solo_momentum(const DevCase &d, SoloShared &sh, bool mixed)
             else s.rho = v[c];
         }
     __syncthreads();
-    solo_bicg_iterate<double>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
+    solo_bicg_iterate<double, WIDE>(d, sh, bi_arrays<double>(d), 0, (long)d.u_max_iter + 1);
 }
 
 // ---- pressure: mixed-precision Jacobi CG (k_cg_*, k_rr_*) ---------------
@@ -3108,6 +3112,7 @@ __device__ __forceinline__ float solo_row(const SoloCg &g, const float *__restri
     return (float)(qa + (ex - so) * (double)pf);
 }
 
+template <bool WIDE>
 __device__ bool solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s);
 
 // The FP32 recurrence of one case in one workgroup, its vectors on the chip:
@@ -3234,11 +3239,12 @@ __device__ void solo_rr(const DevCase &d, SoloShared &sh, KState &s, float *lp)
                 __syncthreads();
             }
         }
-        if ((k + 1) % kReplaceEvery == 0 && solo_rr_replace(d, sh, s)) load_r();
+        if ((k + 1) % kReplaceEvery == 0 && solo_rr_replace<false>(d, sh, s)) load_r();
     }
 }
 
 // residual replacement (k_rr_replace); whether one was made
+template <bool WIDE>
 __device__ bool solo_rr_replace(const DevCase &d, SoloShared &sh, KState &s)
 {
     if (s.done == 1) return false;
@@ -3466,7 +3472,7 @@ __device__ void solo_pressure(const DevCase &d, SoloShared &sh, float *lp, bool 
         const long limit = ((long)d.p_max_iter + 2) * kReplaceEvery;
         for (long k = 0; k < limit && s.done != 1; ++k) {
             if (!s.done) solo_wide_iteration<float>(d, sh, a, s);
-            if ((k + 1) % kReplaceEvery == 0) (void)solo_rr_replace(d, sh, s);
+            if ((k + 1) % kReplaceEvery == 0) (void)solo_rr_replace<true>(d, sh, s);
         }
     } else if (d.N <= 8 * kSolo) solo_rr<8>(d, sh, s, lp);
     else if (d.N <= 16 * kSolo) solo_rr<16>(d, sh, s, lp);
@@ -3520,7 +3526,7 @@ __global__ void __launch_bounds__(kSolo) k_solo_piso(Batch bt, int n_steps, int 
         __syncthreads();
         SOLO_FOR(i, d.N) el_mom_cell(d, i, 0);
         __syncthreads();
-        solo_momentum(d, sh, mixed);
+        solo_momentum<WIDE>(d, sh, mixed);
         int32_t st = FVM_OK;
         for (int c = 0; c < 3; ++c) worst_status(st, sh.ks[c].status);
         if (threadIdx.x == 0)
