@@ -127,7 +127,7 @@ def cg_iteration_bytes(N: int, Fi: int, sell: dict, mixed: bool, diag_cells: int
 
 KERNEL_CLASSES = ["pcg_spmv", "pcg_update", "pcg_dir", "dic_setup", "dic_fwd", "dic_bwd", "bicg_spmv", "mom_face",
                   "mom_cell", "hbya", "p_face", "p_cell", "flux_corr", "U_corr", "pcg32_spmv", "pcg32_update",
-                  "pcg32_dir", "bicg32_spmv"]
+                  "pcg32_dir", "bicg32_spmv", "pcg_resident", "pcg_dic_resident", "pcg32_resident"]
 
 # rocprofv3 kernel names of the classes whose HBM traffic the committed
 # counter summaries hold
@@ -143,13 +143,16 @@ KERNEL_OF_CLASS = {"pcg_spmv": "k_cg_spmv<double", "pcg_update": "k_cg_update<",
 # applications (one at the start, one after each update but the last).
 _P_WORK = ("pcg_spmv", "pcg_update", "pcg_dir", "dic_fwd", "dic_bwd", "pcg32_spmv", "pcg32_update", "pcg32_dir")
 _U_WORK = ("bicg_spmv",)
+# whole pressure solves in one launch: their work is counted in iterations
+_RESIDENT = ("pcg_resident", "pcg_dic_resident", "pcg32_resident")
 
 
 def profile_classes(fvm, case, steps, N, Fi, dic, sell, diag_cells=None):
     """Per-class device time of `steps` PISO steps (HIP events per launch).
 
     mean_us is over every launch (as a kernel trace reports it); us_per_work
-    and alg_GBps are over the launches that did work."""
+    and alg_GBps are over the launches that did work (the iterations of a
+    resident solve)."""
     import torch
     fvm.profile_enable(True)
     p_work = u_work = 0
@@ -163,7 +166,7 @@ def profile_classes(fvm, case, steps, N, Fi, dic, sell, diag_cells=None):
         ms, n = fvm.profile_read(cls)
         if n == 0:
             continue
-        work = min(n, p_work if cls in _P_WORK else u_work if cls in _U_WORK else n)
+        work = p_work if cls in _RESIDENT else min(n, p_work if cls in _P_WORK else u_work if cls in _U_WORK else n)
         mean_us = 1e3 * ms / n
         work_us = 1e3 * ms / max(work, 1)
         b = algorithmic_bytes("pcg_dir_dic" if (cls == "pcg_dir" and dic) else cls, N, Fi, sell, diag_cells)
@@ -172,6 +175,38 @@ def profile_classes(fvm, case, steps, N, Fi, dic, sell, diag_cells=None):
                         alg_bytes=b or None,
                         alg_GBps=round(b / (work_us * 1e-6) / 1e9, 1) if b and work_us > 0 else None)
     fvm.profile_enable(False)
+    return out
+
+
+def profile_product(fvm, case, k, calls=10):
+    """Adds the time of one product with the pressure matrix of the case's
+    last solve (FVM_OP_SPMV) to the classes k: what assembly is compared with
+    where the CG's own products are part of resident solves."""
+    import torch
+    x = torch.ones(case.n_cells, dtype=torch.float64, device="cuda")
+    y = torch.empty_like(x)
+    fvm.operator(case, fvm.OP_SPMV, x, y)
+    torch.cuda.synchronize()
+    fvm.profile_enable(True)
+    for _ in range(calls):
+        fvm.operator(case, fvm.OP_SPMV, x, y)
+    torch.cuda.synchronize()
+    ms, n = fvm.profile_read("op_spmv")
+    fvm.profile_enable(False)
+    us = round(1e3 * ms / max(n, 1), 3)
+    k["op_spmv"] = dict(total_ms=round(ms, 4), launches=n, work_launches=n, mean_us=us, us_per_work=us, alg_bytes=None,
+                        alg_GBps=None)
+
+
+def dic_figures(k, traffic=lambda cls: None):
+    """The DIC solve by kernel class: launched sweeps, or a resident solve per
+    iteration (both sweeps, product, updates)."""
+    out = {}
+    for cls in ("dic_fwd", "dic_bwd", "pcg_dic_resident"):
+        if cls in k:
+            tr = traffic(cls)
+            out[cls] = dict(us_per_work=k[cls]["us_per_work"], alg_GBps=k[cls]["alg_GBps"],
+                            counter_bytes=round(tr["bytes_per_working_launch"]) if tr else None)
     return out
 
 
@@ -406,13 +441,12 @@ def cav100_section(fvm, wl, steps, profile_steps, precond_compare, log):
     if profile_steps > 0:
         pc_ = fvm.Case(spec, mesh=mesh)
         k = profile_classes(fvm, pc_, profile_steps, N, Fi, True, sell, diag_read_cells(spec, sell))
+        if "pcg_spmv" not in k:
+            profile_product(fvm, pc_, k)
         del pc_
         out["kernels"] = k
-        tr = {cls: measured_traffic(cls, "cav100") for cls in ("dic_fwd", "dic_bwd")}
-        out["dic_sweeps"] = {cls: dict(us_per_work=k[cls]["us_per_work"], alg_GBps=k[cls]["alg_GBps"],
-                                       counter_bytes=round(tr[cls]["bytes_per_working_launch"]) if tr[cls] else None)
-                             for cls in ("dic_fwd", "dic_bwd") if cls in k}
-        out["assembly_vs_spmv"] = vs_spmv(k, "pcg_spmv")
+        out["dic_sweeps"] = dic_figures(k, lambda cls: measured_traffic(cls, "cav100"))
+        out["assembly_vs_spmv"] = vs_spmv(k, "pcg_spmv" if "pcg_spmv" in k else "op_spmv")
     out["workload"] = (f"cav100: 3-D lid-driven cavity 100^3 hex cells, random renumbering (seed 2) + RCM, Re=400, "
                        f"PISO dt=0.002, 2 correctors, PCG-DIC / PBiCG tol 1e-7, {steps} steps from rest, FP64 "
                        f"(jacobi, amg: the same with that pressure preconditioner)")
