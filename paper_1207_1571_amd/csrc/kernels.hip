@@ -4877,6 +4877,12 @@ void launch_operator(const BatchSet &bs, int op, const double *in, double *out, 
         break;
     }
     case FVM_OP_DIV: {
+        // cells read several faces while others are written: a result over the
+        // flux needs a copy of it first
+        if (out < in + h.F && in < out + h.N) {
+            (void)hipMemcpyAsync(h.phiH, in, sizeof(double) * (size_t)h.F, hipMemcpyDeviceToDevice, s);
+            in = h.phiH;
+        }
         Prof p("op_div", s);
         run(k_op_div, bs, SZ_CELL, s, in, out);
         break;

@@ -98,3 +98,20 @@ def test_product_after_static_solve_and_dic_apply():
             c.solve_pressure_static(dev(g2), dev(r - r.mean()), torch.zeros(N, dtype=torch.float64, device="cuda"), 1e-8)
         fvm.operator(c, fvm.OP_SPMV, dev(x), out)
         assert _rel(out.cpu().numpy(), _product(case, g2, x)) <= TOL
+
+
+def test_divergence_over_its_input():
+    """The result may lie over the flux it is formed from."""
+    import torch
+    from paper_1207_1571_amd import fvm
+    case = wl.cavity((60, 50, 40), Re=100.0, dt=0.01, perm_seed=4)
+    N, F = case.mesh.n_cells, case.mesh.n_faces
+    flux = torch.from_numpy(np.random.default_rng(13).normal(size=F)).cuda()
+    c = fvm.Case(case)
+    ref = torch.empty(N, dtype=torch.float64, device="cuda")
+    fvm.operator(c, fvm.OP_DIV, flux, ref)
+    for at in (0, F // 3, F - N):
+        both = flux.clone()
+        out = both[at:at + N]
+        fvm.operator(c, fvm.OP_DIV, both, out)
+        assert torch.equal(out, ref), at
