@@ -233,14 +233,18 @@ fvm_status solve_pressure(fvm_case *c, const double *d_gamma_f, const double *d_
 /* solve_pressure_static -- solve_pressure for callers that cannot allocate
  * (code that must not call hipMalloc: under stream capture by the caller's
  * own harness, tight serving loops, harnesses that forbid allocation).  The
- * same system, the same kernels and the same result as solve_pressure with
- * ctl->precond == FVM_PC_JACOBI on an FP64 case; the grid-reduction slots,
- * tickets, Krylov states and a device copy of the case descriptor live in a
- * file-scope device array of 4 MiB (one per GPU, held until the process
- * ends; enough for cases of about 11M cells) instead of the case's
- * workspace; the CG vectors stay in the workspace.  No device or pinned
- * memory is allocated, no graph is captured: iterations are launched
- * directly in chunks of 8 and the stop flag is read back after each chunk.
+ * same system, the same kernels and the same result
+ * as solve_pressure with ctl->precond == FVM_PC_JACOBI on an FP64 case created
+ * with FVM_PC_JACOBI (cases created for another preconditioner run launched
+ * iterations in both); the grid-reduction slots, tickets, Krylov states, the
+ * resident solve's slots and a device copy of the case descriptor live in a
+ * file-scope device array (one per GPU, held until the process ends; 4 MiB of
+ * slots and states, enough for cases of 10 995 712 cells, and 256 KiB behind
+ * them) instead of the case's workspace; the CG vectors stay in the
+ * workspace.  No device or pinned memory is allocated, no graph is captured:
+ * a case with parts for it (up to 1M cells) solves in one launch, another one
+ * by iterations launched directly in chunks of 8, the stop flag read back
+ * after each chunk.
  * Every call on a GPU shares that GPU's array: calls that overlap on one
  * GPU (other streams, other threads) race and must not be made.  The call
  * clears what must start at zero and synchronises before returning.

@@ -303,7 +303,7 @@ struct DevCase {
     double *amg_img;                             // [kAmgTailLds / 8] LDS image of the smallest levels
     double *amg_b[20], *amg_out[20];             // each level's right-hand side and result (host copies)
     // resident pressure CG (PartsHost; res_G == 0: the case has none):
-    // reduction slots (kResSlotWords) and the generation the next solve
+    // reduction slots (kResGens generations of res_gen_words or rr_gen_words) and the generation the next solve
     // starts with, the last solve each part finished; a solve whose waits ran out sets
     // ks[kNumKs - 1].pad[0]
     int32_t res_G, res_W, res_n, res_local, res_halo_max, res_words;

@@ -20,8 +20,8 @@
 // together with others: results do not depend on the batch.
 //
 // Work decomposition: a reducing kernel gives each block 256 consecutive
-// cells; block b runs on XCD b % 8 and its tile index is remapped so that
-// each XCD walks one contiguous eighth of the cells, keeping neighbour
+// cells; blocks b, b + 8, ... run on one XCD and the tile index is remapped
+// so that each XCD walks one contiguous eighth of the cells, keeping neighbour
 // gathers in the L2 of the XCD that produced them.
 //
 // Reductions: wave xor-shuffles, LDS across waves, then a two-level grid
@@ -61,9 +61,10 @@ struct Blk {
     int G;     // blocks of the case
 };
 
-// Blocks are dispatched in index order, round-robin over the 8 XCDs: block
-// raw runs on XCD raw % 8, so XCD x takes tiles [x G/8, (x+1) G/8) and keeps
-// the same cells in every kernel.  rev = 1 walks each XCD's tiles from the
+// Blocks are dispatched in index order, round-robin over the 8 XCDs, a launch
+// going on where the queue's last one ended: block raw runs on XCD
+// (raw + c) % 8, and since the grids are multiples of 8 an XCD takes the tiles
+// [x G/8, (x+1) G/8) with the same x in every kernel.  rev = 1 walks each XCD's tiles from the
 // last one down: a kernel that follows one walked the other way starts on
 // the cells its predecessor touched last, whose lines are the likeliest to
 // be still in the memory-side cache.  Only the time order changes: a tile

@@ -23,10 +23,11 @@
 //
 // Every workgroup of a case must be on the device at once: a launch has at
 // most one per CU, and the host starts it beside other launches only where
-// the CUs suffice for all of them (case.cpp, resident_batch).  Should other work keep a workgroup from starting all
-// the same (another process on the card), the waits end after a time limit:
-// whoever waited marks the solve and leaves, and the host runs the launched
-// iterations from the saved start value instead.
+// the CUs suffice for all of them (case.cpp, resident_batch).  Should other
+// work keep a workgroup from starting all the same (another process on the
+// card), the waits end after a time limit: whoever waited marks the solve and
+// leaves, and the host runs the launched iterations from the saved start
+// value instead, for a while without trying again (resident_outcome).
 //
 // The arithmetic per cell and its order are the launched kernels'; only the
 // order of the sums over cells differs, and it depends on the case's parts
