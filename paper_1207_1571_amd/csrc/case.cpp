@@ -958,6 +958,7 @@ void resident_outcome(bool late)
 }
 
 // The launches of one call in the account, until the call has waited for them.
+constexpr size_t kIdleEvents = 16;   // events kept for later launches
 struct LaunchMark {
     ResidentDevice *R = nullptr;
     std::vector<hipEvent_t> mine;
@@ -965,31 +966,37 @@ struct LaunchMark {
     LaunchMark(const LaunchMark &) = delete;
     LaunchMark &operator=(const LaunchMark &) = delete;
     ~LaunchMark() { clear(); }
-    // the launch just enqueued on s (g_res_mu held)
-    fvm_status add(ResidentDevice *dev, hipStream_t s, int cus, bool solo)
+    // before a launch (g_res_mu held): all that could fail in add
+    fvm_status ready(ResidentDevice *dev)
     {
         R = dev;
-        hipEvent_t e = nullptr;
         mine.reserve(mine.size() + 1);
         R->flight.reserve(R->flight.size() + 1);
-        R->idle.reserve(R->idle.size() + R->flight.size() + 1);
-        if (!R->idle.empty()) {
-            e = R->idle.back();
-            R->idle.pop_back();
-        } else HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        R->idle.reserve(kIdleEvents + 1);
+        if (!R->idle.empty()) return FVM_OK;
+        hipEvent_t e = nullptr;
+        HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        R->idle.push_back(e);
+        return FVM_OK;
+    }
+    // the launch just enqueued on s (g_res_mu held since ready)
+    fvm_status add(hipStream_t s, int cus, bool solo)
+    {
+        const hipEvent_t e = R->idle.back();
+        R->idle.pop_back();
         R->flight.push_back(InFlight{e, s, cus, solo});
         mine.push_back(e);
         HIPCHK(hipEventRecord(e, s));
         return FVM_OK;
     }
-    // they have ended; at most 16 events are kept for later launches
+    // they have ended
     void clear()
     {
         if (mine.empty()) return;
         std::lock_guard<std::mutex> lk(g_res_mu);
         for (hipEvent_t e : mine) {
             R->flight.erase(std::find_if(R->flight.begin(), R->flight.end(), [e](const InFlight &f) { return f.end == e; }));
-            if (R->idle.size() < 16) R->idle.push_back(e);
+            if (R->idle.size() < kIdleEvents) R->idle.push_back(e);
             else (void)hipEventDestroy(e);
         }
         mine.clear();
@@ -1019,6 +1026,8 @@ fvm_status solo_launch(int n, hipStream_t s, LaunchMark &mark, F &&launch)
     ResidentDevice *R = resident_device();
     const int cus = (n + kResGroups - 1) / kResGroups;
     if (R) {
+        fvm_status st = mark.ready(R);
+        if (st != FVM_OK) return st;
         int room = kResGroup;
         const std::vector<InFlight> others = beside(R, s);
         for (const InFlight &f : others) room -= f.cus;
@@ -1031,7 +1040,7 @@ fvm_status solo_launch(int n, hipStream_t s, LaunchMark &mark, F &&launch)
     }
     launch();
     HIPCHK(hipGetLastError());
-    return R ? mark.add(R, s, cus, true) : FVM_OK;
+    return R ? mark.add(s, cus, true) : FVM_OK;
 }
 
 // whole-step launches are in flight: mixed solves, whose launched iterations
@@ -1142,6 +1151,8 @@ std::unique_ptr<ResidentBatch> resident_batch(const ResidentDevice *R, const Dev
 fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solver_ctl *ctl, int serial, hipStream_t s,
                            LaunchMark &mark)
 {
+    fvm_status st = mark.ready(R);
+    if (st != FVM_OK) return st;
     for (hipEvent_t e : rb.behind) HIPCHK(hipStreamWaitEvent(s, e, 0));
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
@@ -1150,7 +1161,7 @@ fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solve
     else if (rb.bs.host[0]->f_x) launch_res_rr(rb.bs, rb.cs, rb.pt, t_res_ticks, serial, s);
     else launch_res_cg(rb.bs, rb.cs, rb.pt, ctl, t_res_ticks, serial, s);
     HIPCHK(hipGetLastError());
-    return mark.add(R, s, rb.cus(), false);
+    return mark.add(s, rb.cus(), false);
 }
 
 fvm_status run_launched(Group &g, int kind, int ctl_src, const fvm_solver_ctl *ctl, std::vector<KState> &res);
