@@ -335,7 +335,8 @@ fvm_status fvm_case_operator(fvm_case *c, int32_t op, const double *d_in, double
  * qualifies for whole-step kernels (FVM_STEP_AUTO above), one launch (one
  * more for cases with more than 6 neighbours per cell) runs all n_steps
  * steps of all cases, one workgroup per case, with no host
- * round trip in between; otherwise every case runs launched phases.
+ * round trip in between (a launch per step while a solve on another stream
+ * that needs the whole device waits for such launches); otherwise every case runs launched phases.
  * infos[i] (may be NULL) receives case i's last-step record.  Each case's
  * result is the same as piso_step on it alone. */
 fvm_status piso_step_batch(fvm_case *const *cases, int32_t n_cases, int32_t n_steps, void *stream,

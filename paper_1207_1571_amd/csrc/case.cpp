@@ -894,6 +894,7 @@ struct ResidentDevice {
     int usable = -1;                // -1: not looked at yet
     bool whole = false;             // it has the CUs the account assumes (not a partition of a card)
     int late = 0;                   // launches in a row whose waits ran out
+    std::chrono::steady_clock::time_point crowded;   // until then, whole steps go one per launch
     std::chrono::steady_clock::time_point again;   // no launch whose workgroups wait for each other before this
     std::vector<InFlight> flight;   // in the order of their launches
     std::vector<hipEvent_t> idle;   // events for the next ones
@@ -1043,6 +1044,18 @@ fvm_status solo_launch(int n, hipStream_t s, LaunchMark &mark, F &&launch)
     return R ? mark.add(s, cus, true) : FVM_OK;
 }
 
+// A solve that needs the CUs of whole-step launches starts behind them, which
+// can be a second of steps: for a while after, such calls launch one step at a
+// time, so that the next solve finds its turn between two steps (a 1M-cell FP64 step
+// beside launches of 32 cases of 24^3 cells and 20 steps: 258 ms before).
+constexpr std::chrono::milliseconds kCrowdedFor(1000);
+bool solo_crowded()
+{
+    std::lock_guard<std::mutex> lk(g_res_mu);
+    const ResidentDevice *R = resident_device();
+    return R && std::chrono::steady_clock::now() < R->crowded;
+}
+
 // whole-step launches are in flight: mixed solves, whose launched iterations
 // give the same bits, then run as these
 bool solo_in_flight()
@@ -1061,6 +1074,7 @@ struct ResidentBatch {
     uint8_t cs[kResParts], pt[kResParts];
     int room;
     std::vector<hipEvent_t> behind;   // launches it starts behind
+    bool crowded = false;             // whole-step launches among them
     explicit ResidentBatch(int room_) : room(std::max(0, room_))
     {
         bs.n = 0;
@@ -1141,6 +1155,7 @@ std::unique_ptr<ResidentBatch> resident_batch(const ResidentDevice *R, const Dev
         for (const InFlight &f : solo) behind.push_back(f.end);
         b.reset(new ResidentBatch(kResGroup));
         (void)b->add(self, d);   // any case fits on the whole device
+        b->crowded = true;
         break;
     }
     b->behind = std::move(behind);
@@ -1154,6 +1169,7 @@ fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solve
     fvm_status st = mark.ready(R);
     if (st != FVM_OK) return st;
     for (hipEvent_t e : rb.behind) HIPCHK(hipStreamWaitEvent(s, e, 0));
+    if (rb.crowded) R->crowded = std::chrono::steady_clock::now() + kCrowdedFor;
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
@@ -1474,7 +1490,10 @@ extern "C" void fvm_resident_test_hook(long ticks, int flags)
     t_res_forget = ticks > 0 && !(flags & 2);
     if (ticks > 0) return;
     std::lock_guard<std::mutex> lk(g_res_mu);
-    if (ResidentDevice *R = resident_device()) R->late = 0;
+    if (ResidentDevice *R = resident_device()) {
+        R->late = 0;
+        R->crowded = {};
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1485,10 +1504,10 @@ namespace {
 // for cases with more than 6 neighbours per cell), one workgroup per case; the kernel leaves each case's last-step record in its
 // Krylov state slots: 0..2 momentum, 3.. the pressure solves, the last one a
 // summary (iters: pressure solves recorded, status: worst over the steps,
-// done: steps completed, first: 1 when a step failed and was rolled back)
-fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
+// done: steps completed, first: 1 when a step failed and was rolled back).
+// infos, failed: per case of the group; all: the worst status so far
+fvm_status piso_solo_launch(Group &g, int32_t n_steps, std::vector<fvm_step_info> &infos, std::vector<char> &failed, int32_t &all)
 {
-    const int n = g.n();
     Phase ph("whole-step launch");
     LaunchMark mark;
     for (const bool wide : {false, true}) {
@@ -1496,40 +1515,73 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
         bs.n = 0;
         for (auto *c : g.cs)
             if (c->wide() == wide) batch_add(bs, c->d.self, &c->d);
-        if (n_steps < 1 || bs.n == 0) continue;
+        if (bs.n == 0) continue;
         fvm_status st = solo_launch(bs.n, g.s, mark, [&] { launch_solo_piso(bs, n_steps, g.cs[0]->o.n_corr, g.s); });
         if (st != FVM_OK) return st;
     }
     std::vector<KState> res;
-    int32_t all = FVM_OK;
-    if (n_steps > 0) {
-        fvm_status st = snapshot(g, res);   // waits for the launch
-        if (st != FVM_OK) return st;
-        mark.clear();
-    }
-    bool failed = false;
-    for (int i = 0; i < n; ++i) {
-        fvm_step_info info{};
-        if (n_steps > 0) {
-            const KState *r = res.data() + (size_t)i * kNumKs;
-            const KState &m = r[kNumKs - 1];
-            for (int c = 0; c < 3; ++c) {
-                to_info(r[c], info.u[c]);
-                worst(info.status, r[c].status);
-            }
-            info.n_p_solves = std::min(m.iters, kNumKs - 4);
-            for (int k = 0; k < info.n_p_solves; ++k) {
-                to_info(r[3 + k], info.p[k]);
-                worst(info.status, r[3 + k].status);
-            }
-            worst(all, m.status);
-            failed = failed || m.first != 0;
-            int32_t &li = g.cs[i]->last_iters[1];
-            li = info.n_p_solves > 0 ? info.p[info.n_p_solves - 1].iters : li;
+    fvm_status st = snapshot(g, res);   // waits for the launch
+    if (st != FVM_OK) return st;
+    mark.clear();
+    infos.assign(g.n(), fvm_step_info{});
+    failed.assign(g.n(), 0);
+    for (int i = 0; i < g.n(); ++i) {
+        fvm_step_info &info = infos[i];
+        const KState *r = res.data() + (size_t)i * kNumKs;
+        const KState &m = r[kNumKs - 1];
+        for (int c = 0; c < 3; ++c) {
+            to_info(r[c], info.u[c]);
+            worst(info.status, r[c].status);
         }
-        if (infos) infos[i] = info;
+        info.n_p_solves = std::min(m.iters, kNumKs - 4);
+        for (int k = 0; k < info.n_p_solves; ++k) {
+            to_info(r[3 + k], info.p[k]);
+            worst(info.status, r[3 + k].status);
+        }
+        worst(all, m.status);
+        failed[i] = m.status < 0 || m.first != 0;
+        int32_t &li = g.cs[i]->last_iters[1];
+        li = info.n_p_solves > 0 ? info.p[info.n_p_solves - 1].iters : li;
     }
-    if (all < 0 || failed)
+    return FVM_OK;
+}
+
+// whole steps of the group's cases: all steps in one launch, or a launch per
+// step while a solve that needs all CUs has to wait for such launches
+// (solo_crowded).  A case whose step failed stays at the start of that step.
+fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
+{
+    std::vector<fvm_case *> cs(g.cs);
+    std::vector<int> idx(g.n());
+    for (int i = 0; i < g.n(); ++i) {
+        idx[i] = i;
+        if (infos) infos[i] = fvm_step_info{};
+    }
+    int32_t all = FVM_OK;
+    bool any = false;
+    std::unique_ptr<Group> rest;   // the cases that go on, once one has failed
+    for (int32_t left = n_steps; left > 0 && !cs.empty();) {
+        const int32_t k = solo_crowded() ? 1 : left;
+        std::vector<fvm_step_info> info;
+        std::vector<char> failed;
+        fvm_status st = piso_solo_launch(rest ? *rest : g, k, info, failed, all);
+        if (st != FVM_OK) return st;
+        left -= k;
+        std::vector<fvm_case *> on;
+        std::vector<int> on_idx;
+        for (size_t j = 0; j < cs.size(); ++j) {
+            if (infos) infos[idx[j]] = info[j];
+            if (failed[j]) continue;
+            on.push_back(cs[j]);
+            on_idx.push_back(idx[j]);
+        }
+        if (on.size() == cs.size()) continue;
+        any = true;
+        cs = on;
+        idx = on_idx;
+        if (!cs.empty()) rest.reset(new Group(cs.data(), (int)cs.size(), g.poll, g.s));
+    }
+    if (all < 0 || any)
         return fvm_fail(all < 0 ? all : FVM_ENUMERIC,
                         "piso: a solve failed (non-finite value or breakdown); the case was rolled back");
     return all;

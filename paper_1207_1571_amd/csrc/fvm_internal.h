@@ -448,9 +448,9 @@ void launch_res_reset(const BatchSet &bs, int serial, hipStream_t s);
 int res_prepare();
 // For tests of waits that run out (not part of the public interface): the
 // calling thread's wait limit (ticks <= 0: the usual one again, and what ran
-// out so far is forgotten); flags 1: its launches leave out their last
-// workgroup, so that every other one waits until the limit; 2: a wait that
-// runs out is remembered as one in earnest is.
+// out or was crowded so far is forgotten); flags 1: its launches leave out
+// their last workgroup, so that every other one waits until the limit; 2: a
+// wait that runs out is remembered as one in earnest is.
 extern "C" void fvm_resident_test_hook(long ticks, int flags);
 // the DIC solve (cases laid out with level parts)
 void launch_res_dic(const BatchSet &bs, const uint8_t *cs, const uint8_t *pt, const fvm_solver_ctl *ctl, long ticks,

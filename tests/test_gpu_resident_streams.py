@@ -2,6 +2,7 @@
 the CUs suffice, wait for each other where they do not, and give the bits that
 each gives alone.
 """
+import ctypes as ct
 import sys
 import threading
 
@@ -94,3 +95,62 @@ def test_solves_of_all_sizes_on_many_streams():
     [t.start() for t in ts]
     [t.join() for t in ts]
     assert not err, err
+
+
+@pytest.fixture
+def forgetful():
+    """What the library remembers of crowded launches ends with the test."""
+    from paper_1207_1571_amd import fvm
+    yield
+    h = fvm.lib().fvm_resident_test_hook
+    h.argtypes, h.restype = [ct.c_long, ct.c_int], None
+    h(0, 0)
+
+
+def test_large_solves_find_their_turn_beside_whole_steps(forgetful):
+    """A case that needs nearly all CUs solves between the steps of whole-step
+    calls, not once per call; both give the bits they give alone.  One of the
+    small cases fails in its first step: it stays as it is, the others go on."""
+    import torch
+    from paper_1207_1571_amd import fvm
+    big = _Solver((128, 96, 84), 5)           # 252 parts
+    ref = big.solve(20)
+    spec = wl.cavity((24, 24, 24), Re=100.0, dt=0.005, precision=wl.MIXED)
+    mesh = fvm.Mesh(spec.mesh, spec.bcs)
+    calls, steps, bad, stream = 3, 40, 5, torch.cuda.Stream()
+
+    def cases():
+        with torch.cuda.stream(stream):
+            cs = [fvm.Case(spec.with_(nu=0.01 + 0.001 * k), stream=stream, mesh=mesh) for k in range(32)]
+            cs[bad].set_state(U=torch.full((cs[bad].n_cells, 3), float("nan"), dtype=torch.float64, device="cuda"))
+        stream.synchronize()
+        return cs
+
+    def run(cs):
+        with torch.cuda.stream(stream):
+            return [fvm.piso_batch(cs, steps, stream=stream, raise_on_case_failure=False)[1] for _ in range(calls)]
+
+    one, two = cases(), cases()
+    infos = run(one)
+    out, err, n = [], [], 0
+
+    def work():
+        try:
+            out.append(run(two))
+        except BaseException as e:   # noqa: BLE001
+            err.append(e)
+
+    t = threading.Thread(target=work)
+    t.start()
+    while t.is_alive():
+        assert np.array_equal(big.solve(20), ref)
+        n += 1
+    t.join()
+    print(f"[streams] {n} large solves beside {calls} calls of {steps} whole steps", file=sys.stderr, flush=True)
+    assert not err, err
+    for a, b in zip(out[0], infos):
+        assert a[bad]["status"] == b[bad]["status"] == fvm.FVM_ENUMERIC
+        assert a[:bad] + a[bad + 1:] == b[:bad] + b[bad + 1:]
+    for a, b in zip(one, two):
+        assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(a.get_state_numpy(), b.get_state_numpy()))
+    assert n >= 10 * calls, n
