@@ -894,7 +894,8 @@ struct ResidentDevice {
     int usable = -1;                // -1: not looked at yet
     bool whole = false;             // it has the CUs the account assumes (not a partition of a card)
     int late = 0;                   // launches in a row whose waits ran out
-    std::chrono::steady_clock::time_point crowded;   // until then, whole steps go one per launch
+    std::chrono::steady_clock::time_point crowded;   // until then, whole steps go one per launch,
+    hipStream_t crowded_by = nullptr;                // but on this stream
     std::chrono::steady_clock::time_point again;   // no launch whose workgroups wait for each other before this
     std::vector<InFlight> flight;   // in the order of their launches
     std::vector<hipEvent_t> idle;   // events for the next ones
@@ -1045,15 +1046,17 @@ fvm_status solo_launch(int n, hipStream_t s, LaunchMark &mark, F &&launch)
 }
 
 // A solve that needs the CUs of whole-step launches starts behind them, which
-// can be a second of steps: for a while after, such calls launch one step at a
-// time, so that the next solve finds its turn between two steps (a 1M-cell FP64
-// step beside launches of 32 cases of 24^3 cells and 20 steps: 258 -> 22 ms).
+// can be a second of steps: for a while after such a solve, calls on other
+// streams launch one step at a time, so that the next solve finds its turn
+// between two steps (a 1M-cell FP64 step beside launches of 32 cases of 24^3
+// cells and 20 steps: 258 -> 22 ms).  Mixed solves do not wait for them.
 constexpr std::chrono::milliseconds kCrowdedFor(1000);
-bool solo_crowded()
+constexpr int kBesideSolo = kResGroup - kMaxBatch / kResGroups;   // CUs per XCD beside a whole-step launch of any size
+bool solo_crowded(hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(g_res_mu);
     const ResidentDevice *R = resident_device();
-    return R && std::chrono::steady_clock::now() < R->crowded;
+    return R && std::chrono::steady_clock::now() < R->crowded && (s != R->crowded_by || s == hipStreamPerThread);
 }
 
 // whole-step launches are in flight: mixed solves, whose launched iterations
@@ -1169,7 +1172,10 @@ fvm_status resident_launch(ResidentDevice *R, ResidentBatch &rb, const fvm_solve
     fvm_status st = mark.ready(R);
     if (st != FVM_OK) return st;
     for (hipEvent_t e : rb.behind) HIPCHK(hipStreamWaitEvent(s, e, 0));
-    if (rb.crowded) R->crowded = std::chrono::steady_clock::now() + kCrowdedFor;
+    if (!rb.bs.host[0]->f_x && (rb.crowded || rb.cus() > kBesideSolo)) {
+        R->crowded = std::chrono::steady_clock::now() + kCrowdedFor;
+        R->crowded_by = s;
+    }
     if (t_res_leave_out)
         for (int b = kResParts - 1; b >= 0; --b)
             if (rb.cs[b] != 255) { rb.cs[b] = 255; break; }
@@ -1562,7 +1568,7 @@ fvm_status piso_solo(Group &g, int32_t n_steps, fvm_step_info *infos)
     bool any = false;
     std::unique_ptr<Group> rest;   // the cases that go on, once one has failed
     for (int32_t left = n_steps; left > 0 && !cs.empty();) {
-        const int32_t k = solo_crowded() ? 1 : left;
+        const int32_t k = solo_crowded(g.s) ? 1 : left;
         std::vector<fvm_step_info> info;
         std::vector<char> failed;
         fvm_status st = piso_solo_launch(rest ? *rest : g, k, info, failed, all);

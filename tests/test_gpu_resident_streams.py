@@ -153,4 +153,6 @@ def test_large_solves_find_their_turn_beside_whole_steps(forgetful):
         assert a[:bad] + a[bad + 1:] == b[:bad] + b[bad + 1:]
     for a, b in zip(one, two):
         assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(a.get_state_numpy(), b.get_state_numpy()))
-    assert n >= 10 * calls, n
+    # one or two per call without that; where the two streams share a hardware
+    # queue, a solve's own round trips each pass a step: some 7 per call
+    assert n >= 4 * calls, n
