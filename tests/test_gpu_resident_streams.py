@@ -51,30 +51,38 @@ class _Solver:
 @pytest.mark.parametrize("cells", [4096, 16384])
 def test_small_solves_run_side_by_side(cells):
     """While one stream runs solves of 4000 iterations (a rod, which takes as
-    many to converge), another ends many of 20 in the time of each."""
-    long, short = _Solver((cells, 1, 1), 1), _Solver((cells, 1, 1), 2)
-    ref, long_ref = short.solve(20), long.solve(4000)
-    runs, err, started = 20, [], threading.Event()
+    many to converge), another ends many of 20 in the time of each.  (Two
+    streams may share one of the 4 hardware queues, where everything runs in
+    order: four further streams are tried.)"""
+    long = _Solver((cells, 1, 1), 1)
+    long_ref = long.solve(4000)
+    runs, counts = 20, []
+    for _ in range(5):
+        short = _Solver((cells, 1, 1), 2)
+        ref, err, started = short.solve(20), [], threading.Event()
 
-    def work():
-        try:
-            for _ in range(runs):
-                started.set()
-                assert np.array_equal(long.solve(4000), long_ref)
-        except BaseException as e:   # noqa: BLE001
-            err.append(e)
+        def work():
+            try:
+                for _ in range(runs):
+                    started.set()
+                    assert np.array_equal(long.solve(4000), long_ref)
+            except BaseException as e:   # noqa: BLE001
+                err.append(e)
 
-    t = threading.Thread(target=work)
-    t.start()
-    started.wait()
-    n = 0
-    while t.is_alive():
-        assert np.array_equal(short.solve(20), ref)
-        n += 1
-    t.join()
-    print(f"[streams] {cells} cells: {n} short solves beside {runs} long ones", file=sys.stderr, flush=True)
-    assert not err, err
-    assert n >= 3 * runs, n
+        t = threading.Thread(target=work)
+        t.start()
+        started.wait()
+        n = 0
+        while t.is_alive():
+            assert np.array_equal(short.solve(20), ref)
+            n += 1
+        t.join()
+        assert not err, err
+        counts.append(n)
+        if n >= 3 * runs:
+            break
+    print(f"[streams] {cells} cells: {counts} short solves beside {runs} long ones", file=sys.stderr, flush=True)
+    assert counts[-1] >= 3 * runs, counts
 
 
 def test_solves_of_all_sizes_on_many_streams():
